@@ -178,11 +178,11 @@ typedef struct fg_tune {
                               fg_render_workspace_size with the same tune), which
                               fg_render_backward reads; 0: not kept (default) */
     int32_t mask_items;    /* at most this many chunks of long ranges get their pass masks
-                              stored by the parallel mask kernel; later chunks compute
-                              them in the blend itself (0: as many as 256 MiB hold) */
+                              made in parallel; ranges past them are blended by one workgroup
+                              each (0: as many as 512 MiB of masks hold) */
     void* blend_events[2]; /* NULL, NULL: none; else two caller-owned hipEvent_t that fg_render
                               records on its stream right before and right after its blend
-                              kernel (k_render), for timing that kernel alone */
+                              kernels (k_render and k_render_long), for timing them alone */
     unsigned long long* bwd_stats; /* NULL: none; else 3 device counters that fg_render_backward
                               adds to (the caller zeroes them): [0] gradient atomic
                               instructions of the blend's backward (one per wave and splat
@@ -348,16 +348,16 @@ size_t fg_render_workspace_size(const fg_camera* cams, int32_t n_views, int64_t 
  * last splat blended, 0 if none. bg is a host array of 3 floats. vals and
  * ranges are fg_sort's for the same views (global splat indices, tiles in
  * global id order). cap_pairs is the capacity the sort ran with (it bounds
- * the range lengths and sizes the workspace). The tiles of all views form
- * one work queue of one persistent blend launch. Long ranges are cut into
- * chunks whose skip tests run in parallel (a first launch writes per-pixel
- * pass masks); the transmittance chain still runs in list order, so results
- * are those of one sequential pass.
+ * the range lengths and sizes the workspace). The tiles of all views are
+ * blended by the same launches. Long ranges are cut into chunks whose skip
+ * tests run in parallel (per-pixel pass masks, walked by a second launch);
+ * the transmittance chain still runs in list order, so results are those of
+ * one sequential pass.
  * frag_stats: NULL, or 8 device counters that the call adds to (the caller
- * zeroes them): [0] (pixel, splat) tests evaluated, [1] tests that reach the
- * exponential (-5.6 <= power <= 0), [2] tests with alpha >= 1/255, [3] splats
- * blended, counted in the blend kernel; [4..6] the same three test counts
- * made by the mask kernel for chunks of long ranges ([7] stays 0). Results do
+ * zeroes them): [0] (pixel, splat) tests evaluated, [1] tests in the range of
+ * the exponential (-5.6 <= power <= 0), [2] tests with alpha >= 1/255, [3] splats
+ * blended; [0..2] count where a range is tested and blended at once, [4..6] are
+ * the same three counts of the pass masks of long ranges ([7] stays 0). Results do
  * not depend on whether counting is on.
  * status is reserved (not written). Errors: FG_ERR_INVALID_ARG,
  * FG_ERR_WORKSPACE. */

@@ -6,33 +6,29 @@
 // stop (T < 1e-4) and the colour sum run sequentially. Tiles near a horizon
 // can hold ~10^4 splats whose pixels seldom saturate, so one workgroup that
 // tests every (pixel, splat) of such a tile would leave the frame waiting on
-// it. The blend therefore runs in two main launches:
+// it. Tiles are therefore told apart (see init_counters for the line):
 //
-//   k_masks   every chunk of CHUNK splats of a "heavy" tile (more than CHUNK
-//             splats) is one work item: per-pixel bit masks of the splats
-//             whose alpha passes the skip tests there go to global memory.
-//             All chunks run in parallel.
-//   k_render  one workgroup per tile, and per half of a heavy tile of 16
-//             or more chunks (heavy work first, items claimed from an atomic
-//             ticket): each
-//             pixel walks the tile's splats in list order, chunk by chunk,
-//             visiting only the marked ones and recomputing alpha with the
-//             same expressions, so every value and decision is bit-identical
-//             to one sequential pass. Light tiles (one lane per pixel)
-//             compute their single chunk's masks in place. In a heavy tile
-//             each wave walks the chunks for its own pixels at its own pace:
-//             64 pixels, or in a split tile 32 with two lanes per pixel
-//             sharing the alphas.
+//   "long" tiles have pass masks (per pixel, the splats that pass the skip
+//   tests) made for all their chunks of CHUNK splats in parallel; then each
+//   pixel walks the tile's splats in list order, chunk by chunk, visiting
+//   only the marked ones and recomputing alpha with the same expressions, two
+//   lanes per pixel sharing the alphas (k_render_long);
+//
+//   the others are blended by one workgroup each, 256 splats at a time, every
+//   8 lanes visiting the splats that can reach their own 4 x 2 pixel block
+//   (fg_blocks.h): each alpha is evaluated once, where it is used, with no
+//   masks and no atomics.
+//
+// k_render makes the masks and blends the tiles that are not long, in one
+// launch; k_render_long follows. Every value and decision is bit-identical to
+// one sequential pass.
 //
 // Before them, k_schedule counts each tile's chunks and orders the tiles that
-// hold splats, and k_tile_prep writes the pixels of the others (background,
-// T = 1) and maps mask items to their tiles.
-//
-// Masks are computed over the (splat, pixel) pairs inside a conservative box
-// per splat (the pixels where its skip test can pass), split evenly over the
-// threads, so few large splats and many small ones balance alike. The launch
-// boundary orders the mask writes before their reads; no workgroup ever
-// waits for another.
+// hold splats ("heavy" ones, of more than one chunk, first), and k_tile_prep
+// writes the pixels of the others (background, T = 1) and maps chunk items to
+// their tiles. The launch boundaries order all writes before their reads; no
+// workgroup ever waits for another.
+#include "fg_blocks.h"
 #include "fg_device.h"
 #include "fg_render_ws.h"
 
@@ -41,25 +37,38 @@ namespace {
 constexpr int kThreads = 256;
 constexpr int kScanThreads = 1024;
 
-// exp(power) <= exp(-5.6) < 1/255 for power < -5.6, so with opacity <= 1 the
-// splat is skipped either way: testing this first avoids evaluating the
-// exponential without changing any result.
-constexpr float kSkipPower = -5.6f;
-
-// Light tiles with fewer splats than this balance their mask work over
-// (splat, pixel) pairs; larger ones give each thread whole splats.
-constexpr int kPairSplats = 128;
-
 struct RenderWs {
     uint32_t* nch;        // [n_tiles] chunks per tile (0: no splats)
-    uint32_t* mfirst;     // [n_tiles] first mask item of a heavy tile
+    uint32_t* mfirst;     // [n_tiles] first chunk item of a heavy tile
     uint32_t* order;      // [n_tiles] tiles in processing order, heavy first
-    uint32_t* mitem;      // [max_mask_items] mask item -> tile
-    uint32_t* counters;   // [0] ticket, [1] heavy tiles, [2] mask items (clamped), [3] tiles with splats
-    uint32_t* masks;      // [max_mask_items][CHUNK/32][256]
-    float* state;         // with save_state: [max_mask_items][4][256] T, C0, C1, C2 after each chunk; else null
+    uint32_t* mitem;      // [max_items] chunk item -> tile
+    uint32_t* counters;   // see the kCnt* indices
+    uint32_t* masks;      // [max_items][CHUNK/32][256] pass masks of the long tiles' chunks
+    float* state;         // with save_state: [max_items][4][256] T, C0, C1, C2 after each chunk; else null
     uint32_t* sched;      // [3][tile blocks] block totals of the many-tile schedule
 };
+
+// counters[]: heavy tiles, chunk items (clamped to max_items), tiles with
+// splats, chunks from which a tile is long.
+//
+// Walking a tile's batches one after another costs about 15 us per batch on
+// the tile's own (the crowded pixel rows of a horizon keep few lanes busy), but
+// 40 % of the work of masks and a second walk. So tiles are long from two
+// chunks on where heavy tiles average four chunks or more (a horizon), or where
+// all chunks together are too few to fill the chip; otherwise (many tiles of
+// much the same length) only tiles of 12 chunks. k_render + k_render_long, both
+// ways: 1M-leaf city (842 chunks on 184 tiles) 97 us long from 2, 290 us from
+// 12; 2M Gaussians in training (21487 on 6937) 1000 us and 343 us.
+enum { kCntHeavy, kCntItems, kCntTiles, kCntLongChunks };
+
+__device__ __forceinline__ void init_counters(uint32_t* __restrict__ counters, uint32_t heavy, uint32_t items,
+                                              uint32_t tiles, int64_t max_items)
+{
+    counters[kCntHeavy] = heavy;
+    counters[kCntItems] = (int64_t)items < max_items ? items : (uint32_t)max_items;
+    counters[kCntTiles] = tiles;
+    counters[kCntLongChunks] = items >= 4u * heavy || items < 1024u ? 2u : 12u;
+}
 
 struct Frag {
     unsigned n_eval, n_exp, n_pass, n_blend;
@@ -100,19 +109,23 @@ __device__ __forceinline__ TileGeom tile_geom(const RenderViews& V, uint32_t t)
     return g;
 }
 
+// Whether a heavy tile of nch chunks (first item mf) is long: its chunks' pass
+// masks are made by k_masks. Every item must have a place in the mask store.
+__device__ __forceinline__ bool is_long(const RenderWs& ws, uint32_t nch, uint32_t mf)
+{
+    return nch >= ws.counters[kCntLongChunks] && mf + nch <= ws.counters[kCntItems];
+}
+
 // One workgroup per tile, after k_schedule: the final values of an empty
 // tile's pixels (background, T = 1, no contributor), so that the blend never
-// visits it, and the mask item -> tile map of a heavy tile's chunks.
-template <int CHUNK>
-__global__ __launch_bounds__(kThreads) void k_tile_prep(int64_t n_tiles, RenderViews V, float bg0,
-                                                        float bg1, float bg2, const uint32_t* __restrict__ nch,
-                                                        const uint32_t* __restrict__ mfirst, int64_t max_mask_items,
-                                                        uint32_t* __restrict__ mitem, float* __restrict__ image,
-                                                        float* __restrict__ final_T,
+// visits it, and the chunk item -> tile map of a heavy tile's chunks.
+__global__ __launch_bounds__(kThreads) void k_tile_prep(int64_t n_tiles, RenderViews V, float bg0, float bg1,
+                                                        float bg2, RenderWs ws, int64_t max_items,
+                                                        float* __restrict__ image, float* __restrict__ final_T,
                                                         uint32_t* __restrict__ n_contrib)
 {
     for (int64_t t = blockIdx.x; t < n_tiles; t += gridDim.x) {
-        const uint32_t c = nch[t];
+        const uint32_t c = ws.nch[t];
         if (c == 0) {
             const TileGeom g = tile_geom(V, (uint32_t)t);
             const int px = g.tx * fgd::kTile + (int)threadIdx.x % fgd::kTile;
@@ -128,9 +141,9 @@ __global__ __launch_bounds__(kThreads) void k_tile_prep(int64_t n_tiles, RenderV
                 n_contrib[g.pix0 + o] = 0u;
             }
         } else if (c > 1) {
-            const uint32_t mf = mfirst[t];
+            const uint32_t mf = ws.mfirst[t];
             for (uint32_t i = threadIdx.x; i < c; i += kThreads)
-                if ((int64_t)(mf + i) < max_mask_items) mitem[mf + i] = (uint32_t)t;
+                if ((int64_t)(mf + i) < max_items) ws.mitem[mf + i] = (uint32_t)t;
         }
     }
 }
@@ -138,15 +151,12 @@ __global__ __launch_bounds__(kThreads) void k_tile_prep(int64_t n_tiles, RenderV
 // One workgroup, one pass: each tile's chunk count (0 for a tile with no
 // splats); lists the tiles that hold splats, heavy ones from the front of
 // order[] in tile order and light ones from its back in reverse tile order;
-// numbers the mask items of heavy tiles (first item per tile) and resets the
-// ticket.
-// With h heavy tiles, work item i of the blend is part i % L of heavy tile
-// order[i / L] for i < L h (L = kHeavyLanes; a heavy tile too short to be
-// split is walked by its part 0, its other parts are empty), else the light
-// tile order[n_tiles - 1 - (i - L h)]. 8 consecutive tiles per thread per
+// numbers the chunk items of heavy tiles (first item per tile). With h heavy
+// tiles, tile i of the blend is order[i] for i < h, else the light tile
+// order[n_tiles - 1 - (i - h)]. 8 consecutive tiles per thread per
 // round (the ranges are read and the chunk counts written with consecutive
 // lanes on consecutive tiles, and handed over through LDS); the running
-// counts of heavy and light tiles (one 64-bit word) and of mask items are
+// counts of heavy and light tiles (one 64-bit word) and of chunk items are
 // scanned together.
 template <int CHUNK>
 __global__ __launch_bounds__(kScanThreads) void k_schedule(const uint32_t* __restrict__ ranges, int64_t n_tiles,
@@ -242,11 +252,8 @@ __global__ __launch_bounds__(kScanThreads) void k_schedule(const uint32_t* __res
         __syncthreads();
     }
     if (tid == 0) {
-        const uint32_t items = s_carry_m;
-        counters[0] = 0u;
-        counters[1] = (uint32_t)s_carry;
-        counters[2] = (int64_t)items < max_mask_items ? items : (uint32_t)max_mask_items;
-        counters[3] = (uint32_t)s_carry + (uint32_t)(s_carry >> 32);
+        const uint32_t heavy = (uint32_t)s_carry;
+        init_counters(counters, heavy, s_carry_m, heavy + (uint32_t)(s_carry >> 32), max_mask_items);
     }
 }
 
@@ -319,10 +326,7 @@ __global__ void k_sched_scan(uint32_t* __restrict__ bsum, int64_t nb, int64_t ma
         l += a1;
         m += a2;
     }
-    counters[0] = 0u;
-    counters[1] = h;
-    counters[2] = (int64_t)m < max_mask_items ? m : (uint32_t)max_mask_items;
-    counters[3] = h + l;
+    init_counters(counters, h, m, h + l, max_mask_items);
 }
 
 template <int CHUNK>
@@ -391,219 +395,6 @@ __global__ __launch_bounds__(kScanThreads) void k_sched_write(int64_t n_tiles, c
     }
 }
 
-using fgd::kNoBox;
-using fgd::splat_box;
-
-// Stage splats [start, start + cnt) of the sorted list into LDS, with their
-// boxes on this tile.
-__device__ __forceinline__ void stage(const float2* __restrict__ xy, const float4* __restrict__ conic_o,
-                                      const float4* __restrict__ rgb_depth, const uint32_t* __restrict__ vals,
-                                      uint32_t start, int cnt, int tx, int ty, int W, int H, float2* s_xy,
-                                      float4* s_co, float4* s_rgb, uint32_t* s_box)
-{
-    for (int j = threadIdx.x; j < cnt; j += kThreads) {
-        const uint32_t g = vals[start + j];
-        const float2 mm = xy[g];
-        const float4 co = conic_o[g];
-        s_xy[j] = mm;
-        s_co[j] = co;
-        if (s_rgb) s_rgb[j] = rgb_depth[g];
-        s_box[j] = splat_box(mm, co, tx, ty, W, H);
-    }
-}
-
-// The skip tests of Eq. (2) for one pixel inside the splat's box: false if
-// power > 0 or power < -5.6 (then alpha < 1/255 since opacity <= 1) or alpha
-// < 1/255; otherwise alpha = min(0.99, opacity exp(power)).
-template <bool STATS>
-__device__ __forceinline__ bool pixel_alpha(float2 mm, float4 co, float fpx, float fpy, float& alpha, Frag& f)
-{
-    const float dx = mm.x - fpx;
-    const float dy = mm.y - fpy;
-    const float power = -0.5f * ((co.x * dx) * dx + (co.z * dy) * dy) - (co.y * dx) * dy;
-    if (STATS) ++f.n_eval;
-    if (power > 0.0f || power < kSkipPower) return false;
-    if (STATS) ++f.n_exp;
-    float a = co.w * fgd::exp_neg_in_range(power);
-    a = a < 0.99f ? a : 0.99f;
-    if (a < 1.0f / 255.0f) return false;
-    if (STATS) ++f.n_pass;
-    alpha = a;
-    return true;
-}
-
-__device__ __forceinline__ uint32_t box_area(uint32_t b)
-{
-    const int x0 = (int)(b & 255u), x1 = (int)((b >> 8) & 255u);
-    const int y0 = (int)((b >> 16) & 255u), y1 = (int)(b >> 24);
-    return x0 <= x1 ? (uint32_t)((x1 - x0 + 1) * (y1 - y0 + 1)) : 0u;
-}
-
-// Exclusive prefix of the staged splats' box areas: s_pref[j] = sum of the
-// areas of splats [0, j), s_pref[cnt] = their total. One thread per S
-// consecutive splats; ends with a barrier.
-template <int CHUNK>
-__device__ __forceinline__ void area_prefix(const uint32_t* s_box, int cnt, uint32_t* s_pref, uint32_t* s_wave)
-{
-    constexpr int S = CHUNK >= kThreads ? CHUNK / kThreads : 1;
-    const int tid = threadIdx.x, lane = fgd::lane_id(), wave = tid / fgd::kWave;
-    uint32_t a[S], sum = 0;
-#pragma unroll
-    for (int k = 0; k < S; k++) {
-        const int j = tid * S + k;
-        a[k] = j < cnt ? box_area(s_box[j]) : 0u;
-        sum += a[k];
-    }
-    uint32_t x = sum;
-#pragma unroll
-    for (int d = 1; d < fgd::kWave; d <<= 1) {
-        const uint32_t y = __shfl_up(x, d, fgd::kWave);
-        if (lane >= d) x += y;
-    }
-    if (lane == fgd::kWave - 1) s_wave[wave] = x;
-    __syncthreads();
-    uint32_t run = x - sum, total = 0;
-#pragma unroll
-    for (int w = 0; w < kThreads / fgd::kWave; w++) {
-        const uint32_t t = s_wave[w];
-        if (w < wave) run += t;
-        total += t;
-    }
-#pragma unroll
-    for (int k = 0; k < S; k++) {
-        const int j = tid * S + k;
-        if (j < cnt) s_pref[j] = run;
-        run += a[k];
-    }
-    if (tid == 0) s_pref[cnt] = total;
-    __syncthreads();
-}
-
-// Pass masks of the staged splats by (splat, pixel) pairs: the pairs inside
-// the splats' boxes, in splat order and rows then columns within a box, are
-// split into equal runs of consecutive pairs, one per thread, so a few large
-// splats and many small ones cost the same per thread. A pair that passes
-// the skip tests sets bit j of its pixel's mask word j/32 (s_mask
-// [word][pixel], zero on entry). Needs area_prefix first.
-template <bool STATS>
-__device__ __forceinline__ void pair_masks(const float2* s_xy, const float4* s_co, const uint32_t* s_box,
-                                           const uint32_t* s_pref, int cnt, int tx, int ty, uint32_t* s_mask,
-                                           Frag& f)
-{
-    const uint32_t total = s_pref[cnt];
-    const uint32_t per = (total + kThreads - 1) / kThreads;
-    uint32_t q = (uint32_t)threadIdx.x * per;
-    const uint32_t qend = q + per < total ? q + per : total;
-    if (q >= qend) return;
-    // the splat holding pair q: the last j with s_pref[j] <= q
-    int lo = 0, hi = cnt;
-    while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (s_pref[mid] <= q) lo = mid; else hi = mid;
-    }
-    int j = lo;
-    uint32_t b = s_box[j];
-    int x0 = (int)(b & 255u), x1 = (int)((b >> 8) & 255u), y0 = (int)((b >> 16) & 255u), y1 = (int)(b >> 24);
-    const uint32_t local = q - s_pref[j];
-    const int w0 = x1 - x0 + 1;
-    int ly = y0 + (int)(local / (uint32_t)w0), lx = x0 + (int)(local % (uint32_t)w0);
-    float2 mm = s_xy[j];
-    float4 co = s_co[j];
-    for (;;) {
-        float alpha;
-        if (pixel_alpha<STATS>(mm, co, (float)(tx * fgd::kTile + lx) + 0.5f, (float)(ty * fgd::kTile + ly) + 0.5f,
-                               alpha, f))
-            atomicOr(&s_mask[(j >> 5) * kThreads + ly * fgd::kTile + lx], 1u << (j & 31));
-        if (++q >= qend) break;
-        if (++lx > x1) {
-            lx = x0;
-            if (++ly > y1) {  // next splat with a non-empty box
-                do {
-                    ++j;
-                } while (s_pref[j + 1] == s_pref[j]);
-                b = s_box[j];
-                x0 = (int)(b & 255u);
-                x1 = (int)((b >> 8) & 255u);
-                y0 = (int)((b >> 16) & 255u);
-                y1 = (int)(b >> 24);
-                lx = x0;
-                ly = y0;
-                mm = s_xy[j];
-                co = s_co[j];
-            }
-        }
-    }
-}
-
-// Narrows [a, b], tile-relative columns of one box row, to the pixels whose
-// centre can pass the skip test of Eq. (2). power >= -5.6 is the ellipse
-// A dx^2 + 2 B dx dy + C dy^2 <= 11.2 (dx, dy: splat centre minus pixel
-// centre), so on a row at offset dy the passing pixel centres lie within
-// u + (B dy -+ sqrt(11.2 A - det dy^2)) / A, det = AC - B^2. The interval is
-// taken for the bound 11.2 * 1.01 and widened by a slack: for a conic with
-// B^2 <= 0.98 AC the float test's rounding moves the form by less than 1e-3,
-// far below the 0.11 added, which also covers the rounding of det, the
-// discriminant, the approximate reciprocal and square root here; so no pixel
-// the test keeps is dropped, and each pixel inside is still tested exactly.
-// Nearly degenerate or non-finite conics keep the whole row. a > b on return
-// when no pixel of the row can pass.
-__device__ __forceinline__ void row_span(float2 mm, float4 co, float fy, int tx, int& a, int& b)
-{
-    const float A = co.x, B = co.y, Cq = co.z;
-    if (!(A > 0.0f) || !(B * B <= 0.98f * (A * Cq))) return;
-    const float dy = mm.y - fy;
-    const float det = A * Cq - B * B;
-    const float disc = (11.2f * 1.01f) * A - det * (dy * dy);
-    if (disc < 0.0f) {
-        b = a - 1;
-        return;
-    }
-    const float inv = __builtin_amdgcn_rcpf(A);
-    const float half = __builtin_amdgcn_sqrtf(disc) * inv;
-    const float cen = (mm.x - (float)(tx * fgd::kTile) - 0.5f) + (B * dy) * inv;
-    const float slack = 0.05f + 1e-4f * (fabsf(cen) + half);
-    const float lo = ceilf(cen - half - slack), hi = floorf(cen + half + slack);
-    // clipped in float (a NaN bound keeps the box column) before converting
-    const float fa = fminf(fmaxf(lo, (float)a), (float)(b + 1));
-    const float fb = fmaxf(fminf(hi, (float)b), (float)(a - 1));
-    a = (int)fa;
-    b = (int)fb;
-}
-
-// Pass masks of one splat (index j of the chunk, box b) on its rows: every
-// pixel of each row's span that passes the skip tests (pixel_alpha) sets bit
-// j of its mask word j/32 (s_mask [word][pixel]).
-template <bool STATS>
-__device__ __forceinline__ void splat_rows(float2 mm, float4 co, uint32_t b, int j, int tx, int ty,
-                                           uint32_t* s_mask, Frag& f)
-{
-    const int x0 = (int)(b & 255u), x1 = (int)((b >> 8) & 255u);
-    const int y0 = (int)((b >> 16) & 255u), y1 = (int)(b >> 24);
-    if (x0 > x1) return;
-    const uint32_t bit = 1u << (j & 31);
-    uint32_t* mrow = s_mask + (j >> 5) * kThreads;
-    for (int ly = y0; ly <= y1; ly++) {
-        const float fy = (float)(ty * fgd::kTile + ly) + 0.5f;
-        int a = x0, e = x1;
-        row_span(mm, co, fy, tx, a, e);
-        for (int lx = a; lx <= e; lx++) {
-            float alpha;
-            if (pixel_alpha<STATS>(mm, co, (float)(tx * fgd::kTile + lx) + 0.5f, fy, alpha, f))
-                atomicOr(&mrow[ly * fgd::kTile + lx], bit);
-        }
-    }
-}
-
-// Splat-parallel pass masks of staged splats: each thread takes whole splats
-// (s_mask zero on entry). Suits many small splats; a few large ones are
-// better served by pair_masks.
-template <bool STATS>
-__device__ __forceinline__ void splat_masks(const float2* s_xy, const float4* s_co, const uint32_t* s_box, int cnt,
-                                            int tx, int ty, uint32_t* s_mask, Frag& f)
-{
-    for (int j = threadIdx.x; j < cnt; j += kThreads) splat_rows<STATS>(s_xy[j], s_co[j], s_box[j], j, tx, ty, s_mask, f);
-}
-
 template <bool STATS, int N>
 __device__ __forceinline__ void flush_stats(const Frag& f, unsigned long long* frag_stats)
 {
@@ -618,60 +409,6 @@ __device__ __forceinline__ void flush_stats(const Frag& f, unsigned long long* f
     }
 }
 
-// alpha of a fragment that passed the skip tests (so -5.6 <= power <= 0):
-// the same expressions as pixel_alpha, hence the same value.
-__device__ __forceinline__ float passed_alpha(float2 mm, float4 co, float fpx, float fpy)
-{
-    const float dx = mm.x - fpx;
-    const float dy = mm.y - fpy;
-    const float power = -0.5f * ((co.x * dx) * dx + (co.z * dy) * dy) - (co.y * dx) * dy;
-    const float alpha = co.w * fgd::exp_neg_in_range(power);
-    return alpha < 0.99f ? alpha : 0.99f;
-}
-
-// Pass masks of the chunks of heavy tiles, one chunk per work item (their
-// splats are mostly small: splat-parallel); masks go to global memory
-// [word][pixel].
-template <int CHUNK, bool STATS>
-__global__ __launch_bounds__(kThreads) void k_masks(const float2* __restrict__ xy, const float4* __restrict__ conic_o,
-                                                    const uint32_t* __restrict__ vals,
-                                                    const uint32_t* __restrict__ ranges, RenderViews V,
-                                                    RenderWs ws, unsigned long long* __restrict__ frag_stats)
-{
-    constexpr int kWords = CHUNK / 32;
-    __shared__ uint32_t s_mask[kWords * kThreads];
-    Frag f = {0, 0, 0, 0};
-    const int tid = threadIdx.x;
-    const uint32_t n_items = ws.counters[2];
-#pragma unroll
-    for (int w = 0; w < kWords; w++) s_mask[w * kThreads + tid] = 0u;
-    __syncthreads();
-    for (uint32_t item = blockIdx.x; item < n_items; item += gridDim.x) {
-        const uint32_t tile = ws.mitem[item];
-        const uint32_t chunk = item - ws.mfirst[tile];
-        const uint32_t r0 = ranges[2 * tile], r1 = ranges[2 * tile + 1];
-        const uint32_t start = r0 + chunk * CHUNK;
-        const int cnt = (int)(r1 - start < (uint32_t)CHUNK ? r1 - start : (uint32_t)CHUNK);
-        const TileGeom tg = tile_geom(V, tile);
-        // each thread its own splats of the chunk, straight from the splat
-        // records (no staging: no other thread reads them)
-        for (int j = tid; j < cnt; j += kThreads) {
-            const uint32_t g = vals[start + j];
-            const float2 mm = xy[g];
-            const float4 co = conic_o[g];
-            splat_rows<STATS>(mm, co, fgd::splat_box(mm, co, tg.tx, tg.ty, tg.W, tg.H), j, tg.tx, tg.ty, s_mask, f);
-        }
-        __syncthreads();
-        uint32_t* out = ws.masks + (size_t)item * (kWords * kThreads);
-#pragma unroll
-        for (int w = 0; w < kWords; w++) {
-            out[w * kThreads + tid] = s_mask[w * kThreads + tid];
-            s_mask[w * kThreads + tid] = 0u;  // this thread's column, for the next item
-        }
-        __syncthreads();
-    }
-    flush_stats<STATS, 3>(f, STATS ? frag_stats + 4 : frag_stats);
-}
 
 struct PixelState {
     float T, C0, C1, C2;
@@ -703,6 +440,258 @@ __device__ __forceinline__ void blend_step(PixelState& p, bool valid, float alph
     if (STATS) f.n_blend += take ? 1u : 0u;
 }
 
+// Walks this lane's block list over one staged batch, four splats at a time:
+// their alphas do not depend on T and are computed together, then the blend
+// steps run in list order. pos0: list position of the batch's first splat.
+template <bool STATS>
+__device__ __forceinline__ void walk(const float4* s_a, const float4* s_b, const float* s_c, const uint8_t* list, int n,
+                                     float fpx, float fpy, uint32_t pos0, PixelState& p, Frag& f)
+{
+    for (int k = 0; k < n && !p.done; k += 4) {
+        const uint32_t e = *reinterpret_cast<const uint32_t*>(list + k);
+        float alpha[4];
+        float4 b[4];
+        float cb[4];
+        bool pass[4];
+#pragma unroll
+        for (int u = 0; u < 4; u++) {
+            const int j = (int)((e >> (8 * u)) & 255u);
+            b[u] = s_b[j];
+            cb[u] = s_c[j];
+            bool in_range;
+            pass[u] = fgb::eval_alpha(s_a[j], b[u], fpx, fpy, alpha[u], in_range) && k + u < n;
+            if (STATS) {
+                f.n_eval += k + u < n ? 1u : 0u;
+                f.n_exp += k + u < n && in_range ? 1u : 0u;
+                f.n_pass += pass[u] ? 1u : 0u;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < 4; u++)
+            blend_step<STATS>(p, pass[u], alpha[u], make_float4(b[u].z, b[u].w, cb[u], 0.0f), pos0 + ((e >> (8 * u)) & 255u),
+                              f);
+    }
+}
+
+// ---- long tiles: pass masks, then the walk -----------------------------------
+
+// Rows and columns of a splat's skip ellipse on one tile: on a row at offset dy
+// from its centre the passing pixel centres lie within u + (B dy -+ sqrt(11.2 A
+// - det dy^2)) / A (see fgb::block_mask for the bound, the slack and the
+// conics that take the conservative box instead).
+struct Spans {
+    float ox, oy, A, B, det, inv;
+    int y0, y1, x0, x1;
+    bool box;  // whole rows of the box
+
+    __device__ __forceinline__ Spans(float2 mm, float4 co, int tx, int ty, int W, int H)
+    {
+        A = co.x;
+        B = co.y;
+        const float C = co.z;
+        box = !(A > 0.0f && B * B <= 0.98f * (A * C));
+        if (box) {
+            const uint32_t b = fgd::splat_box(mm, co, tx, ty, W, H);
+            x0 = (int)(b & 255u);
+            x1 = (int)((b >> 8) & 255u);
+            y0 = (int)((b >> 16) & 255u);
+            y1 = x0 <= x1 ? (int)(b >> 24) : -1;
+            return;
+        }
+        ox = (mm.x - (float)(tx * fgd::kTile)) - 0.5f;
+        oy = (mm.y - (float)(ty * fgd::kTile)) - 0.5f;
+        x0 = 0;
+        x1 = W - 1 - tx * fgd::kTile < 15 ? W - 1 - tx * fgd::kTile : 15;
+        det = A * C - B * B;
+        inv = __builtin_amdgcn_rcpf(A);
+        const float ey = __builtin_amdgcn_sqrtf((fgb::kBound * A) * __builtin_amdgcn_rcpf(det));
+        const float ys = 0.05f + 1e-4f * (fabsf(oy) + ey);
+        const float fa = fmaxf(ceilf(oy - ey - ys), 0.0f);
+        const float fb = fminf(floorf(oy + ey + ys), fminf(15.0f, (float)(H - 1 - ty * fgd::kTile)));
+        y0 = fa <= fb ? (int)fa : 0;
+        y1 = fa <= fb ? (int)fb : -1;
+    }
+
+    __device__ __forceinline__ void row(int ly, int& a, int& e) const
+    {
+        a = x0;
+        e = x1;
+        if (box) return;
+        const float dy = oy - (float)ly;
+        const float disc = fgb::kBound * A - det * (dy * dy);
+        if (disc < 0.0f) {
+            e = a - 1;
+            return;
+        }
+        const float half = __builtin_amdgcn_sqrtf(disc) * inv;
+        const float cen = ox + (B * dy) * inv;
+        const float slack = 0.05f + 1e-4f * (fabsf(cen) + half);
+        // clipped in float (a NaN bound keeps the column) before converting
+        const float fa = fminf(fmaxf(ceilf(cen - half - slack), 0.0f), 16.0f);
+        const float fe = fmaxf(fminf(floorf(cen + half + slack), (float)x1), -1.0f);
+        a = (int)fa;
+        e = (int)fe;
+    }
+};
+
+// Pass masks of the chunks of long tiles, one chunk per work item, to global
+// memory [word][pixel]. Each thread takes a whole splat of the chunk (they are
+// mostly small), straight from the splat records, since no other thread reads
+// them, and tests the pixels of its row spans.
+template <int CHUNK, bool STATS>
+__device__ __forceinline__ void make_masks(uint32_t* s_mask, uint32_t block, uint32_t blocks,
+                                           const float2* __restrict__ xy, const float4* __restrict__ conic_o,
+                                           const uint32_t* __restrict__ vals, const uint32_t* __restrict__ ranges,
+                                           const RenderViews& V, const RenderWs& ws,
+                                           unsigned long long* __restrict__ frag_stats)
+{
+    constexpr int kWords = CHUNK / 32;
+    Frag f = {0, 0, 0, 0};
+    const int tid = threadIdx.x;
+    const uint32_t n_items = ws.counters[kCntItems];
+#pragma unroll
+    for (int w = 0; w < kWords; w++) s_mask[w * kThreads + tid] = 0u;
+    __syncthreads();
+    for (uint32_t item = block; item < n_items; item += blocks) {
+        const uint32_t tile = ws.mitem[item];
+        const uint32_t mf = ws.mfirst[tile];
+        if (!is_long(ws, ws.nch[tile], mf)) continue;
+        const uint32_t start = ranges[2 * tile] + (item - mf) * CHUNK, r1 = ranges[2 * tile + 1];
+        const int cnt = (int)(r1 - start < (uint32_t)CHUNK ? r1 - start : (uint32_t)CHUNK);
+        const TileGeom tg = tile_geom(V, tile);
+        for (int j = tid; j < cnt; j += kThreads) {
+            const uint32_t g = vals[start + j];
+            const float2 mm = xy[g];
+            const float4 co = conic_o[g];
+            const Spans sp(mm, co, tg.tx, tg.ty, tg.W, tg.H);
+            const float4 a = fgb::stage_a(mm, co), b = fgb::stage_b(co, make_float4(0.f, 0.f, 0.f, 0.f));
+            const uint32_t bit = 1u << (j & 31);
+            uint32_t* mrow = s_mask + (j >> 5) * kThreads;
+            for (int ly = sp.y0; ly <= sp.y1; ly++) {
+                const float fy = (float)(tg.ty * fgd::kTile + ly) + 0.5f;
+                int x, e;
+                sp.row(ly, x, e);
+                for (; x <= e; x++) {
+                    float alpha;
+                    bool in_range;
+                    const bool pass =
+                        fgb::eval_alpha(a, b, (float)(tg.tx * fgd::kTile + x) + 0.5f, fy, alpha, in_range);
+                    if (STATS) {
+                        ++f.n_eval;
+                        f.n_exp += in_range ? 1u : 0u;
+                        f.n_pass += pass ? 1u : 0u;
+                    }
+                    if (pass) atomicOr(&mrow[ly * fgd::kTile + x], bit);
+                }
+            }
+        }
+        __syncthreads();
+        uint32_t* out = ws.masks + (size_t)item * (kWords * kThreads);
+#pragma unroll
+        for (int w = 0; w < kWords; w++) {
+            out[w * kThreads + tid] = s_mask[w * kThreads + tid];
+            s_mask[w * kThreads + tid] = 0u;  // this thread's column, for the next item
+        }
+        __syncthreads();
+    }
+    flush_stats<STATS, 3>(f, STATS ? frag_stats + 4 : frag_stats);
+}
+
+__device__ __forceinline__ void write_pixel(const PixelState& p, int px, int py, const TileGeom& tg, float bg0, float bg1,
+                                            float bg2, float* __restrict__ image, float* __restrict__ final_T,
+                                            uint32_t* __restrict__ n_contrib)
+{
+    const size_t o = (size_t)py * tg.W + px;
+    const size_t plane = (size_t)tg.W * tg.H;
+    float* img = image + 3 * tg.pix0;
+    img[o] = p.C0 + p.T * bg0;
+    img[plane + o] = p.C1 + p.T * bg1;
+    img[2 * plane + o] = p.C2 + p.T * bg2;
+    final_T[tg.pix0 + o] = p.T;
+    n_contrib[tg.pix0 + o] = p.last;
+}
+
+// One batch of splats as the workgroup's waves visit it.
+struct Staged {
+    float4 a[fgb::kBatch];
+    float4 b[fgb::kBatch];
+    float c[fgb::kBatch];
+    uint32_t bm[fgb::kBatch];
+    __align__(16) uint8_t list[fgb::kBlocks][fgb::kBatch];
+};
+
+// Blends the n splats of a tile, batch by batch: each thread stages one
+// splat, each wave lists its blocks' splats and walks them. While a batch is
+// walked, the next one's records are loaded into registers. keep: the tile's
+// chunks have items (first: mf), whose state is saved when asked for.
+template <int CHUNK, bool STATS>
+__device__ __forceinline__ void blend_batches(Staged& st, const RenderWs& ws, const float2* __restrict__ xy,
+                                              const float4* __restrict__ conic_o, const float4* __restrict__ rgb_depth,
+                                              const uint32_t* __restrict__ vals, uint32_t n, bool keep, uint32_t nch,
+                                              uint32_t mf, const TileGeom& tg, PixelState& p, Frag& f)
+{
+    constexpr int kBatch = CHUNK < fgb::kBatch ? CHUNK : fgb::kBatch;
+    const int tid = threadIdx.x, wave = tid / fgd::kWave;
+    const int lx = fgb::pixel_x(tid), ly = fgb::pixel_y(tid);
+    const float fpx = (float)(tg.tx * fgd::kTile + lx) + 0.5f, fpy = (float)(tg.ty * fgd::kTile + ly) + 0.5f;
+    const uint32_t n_items = ws.counters[kCntItems];
+    float2 mm;
+    float4 co, c;
+    auto fetch = [&](uint32_t from) {
+        if (tid < kBatch && from + tid < n) {
+            const uint32_t g = vals[from + tid];
+            mm = xy[g];
+            co = conic_o[g];
+            c = rgb_depth[g];
+        }
+    };
+    fetch(0u);
+    for (uint32_t pos = 0; pos < n; pos += kBatch) {
+        const int cnt = (int)(n - pos < (uint32_t)kBatch ? n - pos : (uint32_t)kBatch);
+        if (tid < cnt) {
+            st.a[tid] = fgb::stage_a(mm, co);
+            st.b[tid] = fgb::stage_b(co, c);
+            st.c[tid] = c.z;
+            st.bm[tid] = fgb::block_mask(mm, co, tg.tx, tg.ty, tg.W, tg.H);
+        }
+        __syncthreads();
+        if (pos + kBatch < n) fetch(pos + kBatch);
+        if (__ballot(!p.done) != 0ull) {
+            const int m = fgb::build_lists(st.bm, cnt, st.list + 8 * wave);
+            fgb::wave_sync();
+            walk<STATS>(st.a, st.b, st.c, st.list[tid >> 3], m, fpx, fpy, pos, p, f);
+        }
+        const int alive = __syncthreads_count(!p.done);
+        const bool end = pos + kBatch >= n;
+        if (ws.state && keep && (end || (pos + kBatch) % CHUNK == 0 || alive == 0)) {
+            // once all pixels have stopped, the state after every later chunk equals this one
+            uint32_t ch = pos / CHUNK;
+            const uint32_t ce = alive == 0 ? nch - 1 : ch;
+            for (; ch <= ce && mf + ch < n_items; ch++) {
+                float* to = ws.state + (size_t)(mf + ch) * (4 * kThreads) + ly * fgd::kTile + lx;
+                to[0] = p.T;
+                to[kThreads] = p.C0;
+                to[2 * kThreads] = p.C1;
+                to[3 * kThreads] = p.C2;
+            }
+        }
+        if (alive == 0) break;
+    }
+}
+
+// ---- the walk of a long tile ---------------------------------------------------
+
+// alpha of a fragment that passed the skip tests (so -5.6 <= power <= 0):
+// the same expressions as pixel_alpha, hence the same value.
+__device__ __forceinline__ float passed_alpha(float2 mm, float4 co, float fpx, float fpy)
+{
+    const float dx = mm.x - fpx;
+    const float dy = mm.y - fpy;
+    const float power = -0.5f * ((co.x * dx) * dx + (co.z * dy) * dy) - (co.y * dx) * dy;
+    const float alpha = co.w * fgd::exp_neg_in_range(power);
+    return alpha < 0.99f ? alpha : 0.99f;
+}
+
 // Walks the marked splats of one staged chunk for this lane's pixel. mcol
 // points at the pixel's first mask word (words STRIDE apart). A summary
 // bit per 64-splat pair of words, read first, sends the lane straight to the
@@ -711,56 +700,35 @@ __device__ __forceinline__ void blend_step(PixelState& p, bool valid, float alph
 // reads and arithmetic overlap; the blend steps then run strictly in list
 // order.
 //
-// With LPP > 1 lanes per pixel (heavy tiles), the LPP lanes of a pixel hold
-// the same mask words and state and run the same steps in lockstep; lane
-// `sub` of the pixel computes the alphas of group positions sub, sub + LPP,
-// ..., and the group's alphas are exchanged across the pixel's lanes (which
-// lie 64 / LPP apart) before the blend steps, so each lane evaluates 4 / LPP
-// exponentials per group instead of 4. Every lane then applies the same
-// steps to the same values, and the results equal the one-lane walk's.
-template <int LPP>
+// The two lanes of a pixel (32 apart) hold the same mask words and state and
+// run the same steps in lockstep; lane `sub` of the pixel computes the alphas
+// of group positions sub and sub + 2, and the group's alphas are exchanged
+// before the blend steps, so each lane evaluates two exponentials per group
+// instead of four. Both then apply the same steps to the same values, and the
+// results equal a one-lane walk's.
+constexpr int kPixels = fgd::kWave / 2;  // pixels per wave
+
 __device__ __forceinline__ void group_alphas(const float2* s_xy, const float4* s_co, float fpx, float fpy, int sub,
                                              int j0, int j1, int j2, int j3, float& a0, float& a1, float& a2,
                                              float& a3)
 {
-    constexpr int P = fgd::kWave / LPP;
-    if constexpr (LPP == 1) {
-        a0 = passed_alpha(s_xy[j0], s_co[j0], fpx, fpy);
-        a1 = passed_alpha(s_xy[j1], s_co[j1], fpx, fpy);
-        a2 = passed_alpha(s_xy[j2], s_co[j2], fpx, fpy);
-        a3 = passed_alpha(s_xy[j3], s_co[j3], fpx, fpy);
-    } else if constexpr (LPP == 2) {
-        const int ja = sub ? j1 : j0, jb = sub ? j3 : j2;
-        const float ma = passed_alpha(s_xy[ja], s_co[ja], fpx, fpy);
-        const float mb = passed_alpha(s_xy[jb], s_co[jb], fpx, fpy);
-        const float oa = __shfl_xor(ma, P, fgd::kWave);
-        const float ob = __shfl_xor(mb, P, fgd::kWave);
-        a0 = sub ? oa : ma;
-        a1 = sub ? ma : oa;
-        a2 = sub ? ob : mb;
-        a3 = sub ? mb : ob;
-    } else {
-        static_assert(LPP == 4, "1, 2 or 4 lanes per pixel");
-        const int jm = sub == 0 ? j0 : sub == 1 ? j1 : sub == 2 ? j2 : j3;
-        const float m = passed_alpha(s_xy[jm], s_co[jm], fpx, fpy);
-        // the alpha of position k sits on the pixel's lane k, i.e. at lane
-        // distance (k ^ sub) * P
-        const float x1 = __shfl_xor(m, P, fgd::kWave);
-        const float x2 = __shfl_xor(m, 2 * P, fgd::kWave);
-        const float x3 = __shfl_xor(m, 3 * P, fgd::kWave);
-        const auto pick = [&](int d) { return d == 0 ? m : d == 1 ? x1 : d == 2 ? x2 : x3; };
-        a0 = pick(sub);
-        a1 = pick(1 ^ sub);
-        a2 = pick(2 ^ sub);
-        a3 = pick(3 ^ sub);
-    }
+    const int ja = sub ? j1 : j0, jb = sub ? j3 : j2;
+    const float ma = passed_alpha(s_xy[ja], s_co[ja], fpx, fpy);
+    const float mb = passed_alpha(s_xy[jb], s_co[jb], fpx, fpy);
+    const float oa = __shfl_xor(ma, kPixels, fgd::kWave);
+    const float ob = __shfl_xor(mb, kPixels, fgd::kWave);
+    a0 = sub ? oa : ma;
+    a1 = sub ? ma : oa;
+    a2 = sub ? ob : mb;
+    a3 = sub ? mb : ob;
 }
 
-template <int CHUNK, bool STATS, int STRIDE, int LPP = 1>
-__device__ __forceinline__ void walk(const uint32_t* mcol, const float2* s_xy, const float4* s_co,
+template <int CHUNK, bool STATS>
+__device__ __forceinline__ void walk_masks(const uint32_t* mcol, const float2* s_xy, const float4* s_co,
                                      const float4* s_rgb, float fpx, float fpy, uint32_t base, PixelState& p,
-                                     Frag& f, int sub = 0)
+                                     Frag& f, int sub)
 {
+    constexpr int STRIDE = fgd::kWave;
     constexpr int kPairs = CHUNK / 64;
     uint32_t summary = 0;
 #pragma unroll
@@ -785,7 +753,7 @@ __device__ __forceinline__ void walk(const uint32_t* mcol, const float2* s_xy, c
             const int j3 = v3 ? b + __builtin_ctzll(m) : j0;
             m &= m - 1ull;
             float a0, a1, a2, a3;
-            group_alphas<LPP>(s_xy, s_co, fpx, fpy, sub, j0, j1, j2, j3, a0, a1, a2, a3);
+            group_alphas(s_xy, s_co, fpx, fpy, sub, j0, j1, j2, j3, a0, a1, a2, a3);
             const float4 c0 = s_rgb[j0], c1 = s_rgb[j1], c2 = s_rgb[j2], c3 = s_rgb[j3];
             blend_step<STATS>(p, true, a0, c0, base + (uint32_t)j0, f);
             blend_step<STATS>(p, v1, a1, c1, base + (uint32_t)j1, f);
@@ -795,7 +763,7 @@ __device__ __forceinline__ void walk(const uint32_t* mcol, const float2* s_xy, c
     }
 }
 
-// Register copy of one chunk for one wave of a heavy tile: the splat records
+// Register copy of one chunk for one wave of a long tile: the splat records
 // this lane stages (every 64th of the chunk) and the mask words of its pixel
 // (zero where the masks are computed in place).
 template <int CHUNK>
@@ -832,7 +800,7 @@ __device__ __forceinline__ void fetch_chunk(const float2* __restrict__ xy, const
                                             const float4* __restrict__ rgb_depth, const uint32_t* __restrict__ masks,
                                             uint32_t r0, uint32_t r1, uint32_t chunk,
                                             const uint32_t (&g)[ChunkRegs<CHUNK>::S], uint32_t mf,
-                                            uint32_t n_mask_items, int pix, ChunkRegs<CHUNK>& R)
+                                            int pix, ChunkRegs<CHUNK>& R)
 {
     const int cnt = chunk_count<CHUNK>(r0, r1, chunk);
 #pragma unroll
@@ -848,244 +816,144 @@ __device__ __forceinline__ void fetch_chunk(const float2* __restrict__ xy, const
             R.rgb[k] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
         }
     }
-    if (mf + chunk < n_mask_items) {
-        const uint32_t* src = masks + (size_t)(mf + chunk) * (CHUNK / 32 * kThreads);
+    const uint32_t* src = masks + (size_t)(mf + chunk) * (CHUNK / 32 * kThreads);
 #pragma unroll
-        for (int w = 0; w < CHUNK / 32; w++) R.m[w] = src[w * kThreads + pix];
-    } else {
-#pragma unroll
-        for (int w = 0; w < CHUNK / 32; w++) R.m[w] = 0u;
-    }
+    for (int w = 0; w < CHUNK / 32; w++) R.m[w] = src[w * kThreads + pix];
 }
 
-// Orders this wave's LDS writes before its own later LDS reads (and reads
-// before later writes); no other wave takes part.
-__device__ __forceinline__ void wave_sync()
+// The long tiles, two work items each (the upper and lower 8 pixel rows), 32
+// pixels per wave with two lanes per pixel. Each wave walks the chunks for its
+// own pixels at its own pace, with its own staging area, so no wave waits on
+// the others between chunks. While one chunk is walked, the next chunk's
+// splat records and masks are loaded into registers, and the indices of the
+// chunk after it. What bounds it is the walk of the longest lists: two lanes
+// per pixel in every long tile took 66 us on the 1M-leaf city and 196 us on the
+// 20M-node one at 1440p, only from 10 chunks on 101 and 234 us.
+template <int CHUNK, bool STATS>
+__global__ __launch_bounds__(kThreads) void k_render_long(const float2* __restrict__ xy,
+                                                          const float4* __restrict__ conic_o,
+                                                          const float4* __restrict__ rgb_depth,
+                                                          const uint32_t* __restrict__ vals,
+                                                          const uint32_t* __restrict__ ranges, RenderViews V, float bg0,
+                                                          float bg1, float bg2, RenderWs ws, float* __restrict__ image,
+                                                          float* __restrict__ final_T, uint32_t* __restrict__ n_contrib,
+                                                          unsigned long long* __restrict__ frag_stats)
 {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-// Pass masks of a staged chunk for the 64 / LPP pixels of one wave (rows
-// y0 .. y0 + 4 / LPP - 1 of the tile), when the chunk's masks were not
-// stored: each lane takes every 64th splat and tests the pixels of its box
-// in those rows. w_mask [word][64] is zero on entry; a pixel's bits go to
-// each of its LPP lanes' columns.
-template <bool STATS, int LPP>
-__device__ __forceinline__ void wave_masks(const float2* w_xy, const float4* w_co, int cnt, int tx, int ty, int W,
-                                           int H, int y0, uint32_t* w_mask, Frag& f)
-{
-    constexpr int P = fgd::kWave / LPP;
-    constexpr int kRows = P / fgd::kTile;
-    for (int j = fgd::lane_id(); j < cnt; j += fgd::kWave) {
-        const float2 mm = w_xy[j];
-        const float4 co = w_co[j];
-        const uint32_t b = splat_box(mm, co, tx, ty, W, H);
-        const int x0 = (int)(b & 255u), x1 = (int)((b >> 8) & 255u);
-        const int by0 = (int)((b >> 16) & 255u), by1 = (int)(b >> 24);
-        if (x0 > x1) continue;
-        const int ya = by0 > y0 ? by0 : y0, yb = by1 < y0 + kRows - 1 ? by1 : y0 + kRows - 1;
-        const uint32_t bit = 1u << (j & 31);
-        uint32_t* mrow = w_mask + (j >> 5) * fgd::kWave;
-        for (int ly = ya; ly <= yb; ly++) {
-            const float fy = (float)(ty * fgd::kTile + ly) + 0.5f;
-            int a = x0, b = x1;
-            row_span(mm, co, fy, tx, a, b);
-            for (int lx = a; lx <= b; lx++) {
-                float alpha;
-                if (pixel_alpha<STATS>(mm, co, (float)(tx * fgd::kTile + lx) + 0.5f, fy, alpha, f)) {
+    constexpr int kWords = CHUNK / 32;
+    constexpr int kWaves = kThreads / fgd::kWave;
+    __shared__ float2 s_xy[kWaves * CHUNK];
+    __shared__ float4 s_co[kWaves * CHUNK];
+    __shared__ float4 s_rgb[kWaves * CHUNK];
+    __shared__ uint32_t s_mask[kWords * kThreads];
+    const int tid = threadIdx.x;
+    const int wave = tid / fgd::kWave, lane = fgd::lane_id();
+    const int sub = lane / kPixels;  // this lane's place among its pixel's lanes
+    const uint32_t n_work = 2u * ws.counters[kCntHeavy];
+    Frag f = {0, 0, 0, 0};
+    for (uint32_t item = blockIdx.x; item < n_work; item += gridDim.x) {
+        const uint32_t tile = ws.order[item / 2];
+        const uint32_t nch = ws.nch[tile], mf = ws.mfirst[tile];
+        if (!is_long(ws, nch, mf)) continue;
+        const int pix = (int)(item % 2) * (kThreads / 2) + wave * kPixels + lane % kPixels;
+        const uint32_t r0 = ranges[2 * tile], r1 = ranges[2 * tile + 1];
+        const TileGeom tg = tile_geom(V, tile);
+        const int px = tg.tx * fgd::kTile + pix % fgd::kTile, py = tg.ty * fgd::kTile + pix / fgd::kTile;
+        const bool inside = px < tg.W && py < tg.H;
+        const float fpx = (float)px + 0.5f, fpy = (float)py + 0.5f;
+        PixelState p = {1.0f, 0.0f, 0.0f, 0.0f, 0u, !inside};
+        float2* w_xy = s_xy + wave * CHUNK;
+        float4* w_co = s_co + wave * CHUNK;
+        float4* w_rgb = s_rgb + wave * CHUNK;
+        uint32_t* w_mask = s_mask + wave * (kWords * fgd::kWave);
+        ChunkRegs<CHUNK> R;
+        uint32_t gnext[ChunkRegs<CHUNK>::S];
+        {
+            uint32_t g0[ChunkRegs<CHUNK>::S];
+            fetch_vals<CHUNK>(vals, r0, r1, 0u, g0);
+            fetch_chunk<CHUNK>(xy, conic_o, rgb_depth, ws.masks, r0, r1, 0u, g0, mf, pix, R);
+            fetch_vals<CHUNK>(vals, r0, r1, 1u, gnext);
+        }
+        auto save_state = [&](uint32_t ch) {  // per-pixel state after this chunk, for the backward
+            float* st = ws.state + (size_t)(mf + ch) * (4 * kThreads) + pix;
+            st[0] = p.T;
+            st[kThreads] = p.C0;
+            st[2 * kThreads] = p.C1;
+            st[3 * kThreads] = p.C2;
+        };
+        const unsigned n_blend0 = f.n_blend;
+        uint32_t chunk = 0;
+        for (; chunk < nch; chunk++) {
+            // the wave stops once all of its pixels have terminated
+            if (__ballot(!p.done) == 0ull) break;
+            const int cnt = chunk_count<CHUNK>(r0, r1, chunk);
+            fgb::wave_sync();  // the previous chunk's reads are done
 #pragma unroll
-                    for (int c = 0; c < LPP; c++) atomicOr(&mrow[c * P + (ly - y0) * fgd::kTile + lx], bit);
+            for (int k = 0; k < ChunkRegs<CHUNK>::S; k++) {
+                const int j = k * fgd::kWave + lane;
+                if (j < cnt) {
+                    w_xy[j] = R.xy[k];
+                    w_co[j] = R.co[k];
+                    w_rgb[j] = R.rgb[k];
                 }
             }
+#pragma unroll
+            for (int w = 0; w < kWords; w++) w_mask[w * fgd::kWave + lane] = R.m[w];
+            fgb::wave_sync();
+            if (chunk + 1 < nch) {
+                fetch_chunk<CHUNK>(xy, conic_o, rgb_depth, ws.masks, r0, r1, chunk + 1, gnext, mf, pix, R);
+                if (chunk + 2 < nch) fetch_vals<CHUNK>(vals, r0, r1, chunk + 2, gnext);
+            }
+            walk_masks<CHUNK, STATS>(w_mask + lane, w_xy, w_co, w_rgb, fpx, fpy, chunk * CHUNK, p, f, sub);
+            if (ws.state && sub == 0) save_state(chunk);
         }
+        if (ws.state && sub == 0)  // the state after every later chunk equals the final one
+            for (; chunk < nch; chunk++) save_state(chunk);
+        if (STATS && sub != 0) f.n_blend = n_blend0;  // a pixel's blends count on its first lane only
+        if (inside && sub == 0) write_pixel(p, px, py, tg, bg0, bg1, bg2, image, final_T, n_contrib);
     }
+    flush_stats<STATS, 4>(f, frag_stats);
 }
 
-// Lanes per pixel in the walk of a long heavy tile: such a tile is
-// kHeavyLanes work items of 256 / kHeavyLanes pixels each. Two halve the
-// exponentials on the longest tiles' critical path; four cost more in
-// staging (every wave stages whole chunks) than they save. Only tiles of at
-// least kSplitChunks chunks are split: for shorter ones the doubled staging
-// outweighs the shorter walk (the blend was fastest at 16 among 2 to 48).
-constexpr int kHeavyLanes = 2;
-constexpr int kSplitChunks = 16;
-
-template <int CHUNK, bool STATS, int LPP>
+// The first mask_blocks workgroups make the long tiles' pass masks; the others
+// blend the tiles that hold splats and are not long, one each, heavy ones
+// first (those past the last find nothing). One launch, since the two need
+// nothing of each other and neither fills the chip by itself in most frames.
+// The dispatcher balances the tiles: a work ticket (one atomic per tile, all
+// on one address) took longer than the tiles themselves in frames of few
+// splats.
+template <int CHUNK, bool STATS>
 __global__ __launch_bounds__(kThreads) void k_render(const float2* __restrict__ xy, const float4* __restrict__ conic_o,
                                                      const float4* __restrict__ rgb_depth,
                                                      const uint32_t* __restrict__ vals,
                                                      const uint32_t* __restrict__ ranges, int64_t n_tiles,
                                                      RenderViews V, float bg0, float bg1, float bg2, RenderWs ws,
-                                                     float* __restrict__ image, float* __restrict__ final_T,
-                                                     uint32_t* __restrict__ n_contrib,
+                                                     uint32_t mask_blocks, float* __restrict__ image,
+                                                     float* __restrict__ final_T, uint32_t* __restrict__ n_contrib,
                                                      unsigned long long* __restrict__ frag_stats)
 {
-    constexpr int kWords = CHUNK / 32;
-    constexpr int kWaves = kThreads / fgd::kWave;
-    // a light tile uses the first CHUNK records; a heavy tile gives each wave
-    // its own CHUNK records and its pixels' mask columns
-    __shared__ float2 s_xy[kWaves * CHUNK];
-    __shared__ float4 s_co[kWaves * CHUNK];
-    __shared__ float4 s_rgb[kWaves * CHUNK];
-    __shared__ uint32_t s_mask[kWords * kThreads];
-    __shared__ uint32_t s_box[CHUNK];
-    __shared__ uint32_t s_pref[CHUNK + 1];
-    __shared__ uint32_t s_wave[kWaves];
-    __shared__ uint32_t s_item;
-    constexpr int P = fgd::kWave / LPP;  // pixels per wave in a heavy tile
-    const int tid = threadIdx.x;
-    const int wave = tid / fgd::kWave, lane = fgd::lane_id();
-    const uint32_t n_mask_items = ws.counters[2];
-    const uint32_t n_heavy = ws.counters[1];
-    // each heavy tile is LPP items (parts of 256 / LPP pixels), each light tile one
-    const uint32_t n_work = ws.counters[3] + (uint32_t)(LPP - 1) * n_heavy;
-    Frag f = {0, 0, 0, 0};
-    if (tid == 0) s_item = atomicAdd(&ws.counters[0], 1u);
-    __syncthreads();
-    for (;;) {
-        const uint32_t item = s_item;
-        if (item >= n_work) break;
-        const bool heavy_item = item < (uint32_t)LPP * n_heavy;
-        const uint32_t tile = ws.order[heavy_item ? (int64_t)(item / LPP)
-                                                  : n_tiles - 1 - (int64_t)(item - (uint32_t)LPP * n_heavy)];
-        const uint32_t nch = ws.nch[tile];
-        // a heavy tile with fewer than kSplitChunks chunks is walked whole by
-        // its first item, one lane per pixel; its other items are empty
-        const bool split = LPP > 1 && heavy_item && nch >= (uint32_t)kSplitChunks;
-        const int part = heavy_item ? (int)(item % LPP) : 0;
-        if (heavy_item && !split && part != 0) {
-            __syncthreads();
-            if (tid == 0) s_item = atomicAdd(&ws.counters[0], 1u);
-            __syncthreads();
-            continue;
-        }
-        const int sub = split ? lane / P : 0;  // this lane's place among its pixel's lanes
-        const int pix = split ? part * (kThreads / LPP) + wave * P + lane % P : tid;
-        const int lx = pix % fgd::kTile, ly = pix / fgd::kTile;
-        const uint32_t r0 = ranges[2 * tile], r1 = ranges[2 * tile + 1];
-        // Tiles are ordered heavy first, so a light tile is followed only by
-        // light ones: its workgroup claims the next tile now, hiding the
-        // atomic's latency. A heavy tile's workgroup does not, so no tile
-        // waits behind a long one.
-        uint32_t next_item = 0;
-        if (tid == 0 && nch <= 1) next_item = atomicAdd(&ws.counters[0], 1u);
-        const uint32_t mf = nch > 1 ? ws.mfirst[tile] : 0u;
-        const TileGeom tg = tile_geom(V, tile);
-        const int tx = tg.tx, ty = tg.ty, W = tg.W, H = tg.H;
-        const int px = tx * fgd::kTile + lx;
-        const int py = ty * fgd::kTile + ly;
-        const bool inside = px < W && py < H;
-        const float fpx = (float)px + 0.5f, fpy = (float)py + 0.5f;
-        PixelState p = {1.0f, 0.0f, 0.0f, 0.0f, 0u, !inside};
-        if (nch <= 1) {
-            // light tile: one chunk, masks computed here
-            const int cnt = (int)(r1 - r0);
-#pragma unroll
-            for (int w = 0; w < kWords; w++) s_mask[w * kThreads + tid] = 0u;
-            stage(xy, conic_o, rgb_depth, vals, r0, cnt, tx, ty, W, H, s_xy, s_co, s_rgb, s_box);
-            __syncthreads();
-            if (cnt < kPairSplats) {
-                area_prefix<CHUNK>(s_box, cnt, s_pref, s_wave);
-                pair_masks<STATS>(s_xy, s_co, s_box, s_pref, cnt, tx, ty, s_mask, f);
-            } else {
-                splat_masks<STATS>(s_xy, s_co, s_box, cnt, tx, ty, s_mask, f);
-            }
-            __syncthreads();
-            walk<CHUNK, STATS, kThreads>(s_mask + tid, s_xy, s_co, s_rgb, fpx, fpy, 0u, p, f);
-        } else {
-            // heavy tile: each wave walks the chunks for its own 64 / LPP
-            // pixels at its own pace, with its own staging area, so no wave waits on the
-            // others between chunks. While one chunk is walked, the next
-            // chunk's splat records and stored masks are loaded into
-            // registers, and the indices of the chunk after it.
-            float2* w_xy = s_xy + wave * CHUNK;
-            float4* w_co = s_co + wave * CHUNK;
-            float4* w_rgb = s_rgb + wave * CHUNK;
-            uint32_t* w_mask = s_mask + wave * (kWords * fgd::kWave);
-            ChunkRegs<CHUNK> R;
-            uint32_t gnext[ChunkRegs<CHUNK>::S];
-            {
-                uint32_t g0[ChunkRegs<CHUNK>::S];
-                fetch_vals<CHUNK>(vals, r0, r1, 0u, g0);
-                fetch_chunk<CHUNK>(xy, conic_o, rgb_depth, ws.masks, r0, r1, 0u, g0, mf, n_mask_items, pix, R);
-                fetch_vals<CHUNK>(vals, r0, r1, 1u, gnext);
-            }
-            const unsigned n_blend0 = f.n_blend;
-            uint32_t chunk = 0;
-            for (; chunk < nch; chunk++) {
-                // the wave stops once all of its pixels have terminated
-                if (__ballot(!p.done) == 0ull) break;
-                const int cnt = chunk_count<CHUNK>(r0, r1, chunk);
-                const bool stored = mf + chunk < n_mask_items;
-                wave_sync();  // the previous chunk's reads are done
-#pragma unroll
-                for (int k = 0; k < ChunkRegs<CHUNK>::S; k++) {
-                    const int j = k * fgd::kWave + lane;
-                    if (j < cnt) {
-                        w_xy[j] = R.xy[k];
-                        w_co[j] = R.co[k];
-                        w_rgb[j] = R.rgb[k];
-                    }
-                }
-                // zero where the masks are computed here
-#pragma unroll
-                for (int w = 0; w < kWords; w++) w_mask[w * fgd::kWave + lane] = R.m[w];
-                wave_sync();
-                if (chunk + 1 < nch) {
-                    fetch_chunk<CHUNK>(xy, conic_o, rgb_depth, ws.masks, r0, r1, chunk + 1, gnext, mf, n_mask_items,
-                                       pix, R);
-                    if (chunk + 2 < nch) fetch_vals<CHUNK>(vals, r0, r1, chunk + 2, gnext);
-                }
-                if (!stored) {  // beyond the mask store: masks computed here
-                    if (split)
-                        wave_masks<STATS, LPP>(w_xy, w_co, cnt, tx, ty, W, H, (pix - lane % P) / fgd::kTile, w_mask,
-                                               f);
-                    else
-                        wave_masks<STATS, 1>(w_xy, w_co, cnt, tx, ty, W, H, wave * (fgd::kWave / fgd::kTile), w_mask,
-                                             f);
-                    wave_sync();
-                }
-                if (split)
-                    walk<CHUNK, STATS, fgd::kWave, LPP>(w_mask + lane, w_xy, w_co, w_rgb, fpx, fpy, chunk * CHUNK, p,
-                                                        f, sub);
-                else
-                    walk<CHUNK, STATS, fgd::kWave, 1>(w_mask + lane, w_xy, w_co, w_rgb, fpx, fpy, chunk * CHUNK, p, f);
-                if (ws.state && stored && sub == 0) {  // per-pixel state after this chunk, for the backward
-                    float* st = ws.state + (size_t)(mf + chunk) * (4 * kThreads);
-                    st[pix] = p.T;
-                    st[kThreads + pix] = p.C0;
-                    st[2 * kThreads + pix] = p.C1;
-                    st[3 * kThreads + pix] = p.C2;
-                }
-            }
-            // the state after every later chunk equals the final one
-            if (ws.state && sub == 0) {
-                for (; chunk < nch && mf + chunk < n_mask_items; chunk++) {
-                    float* st = ws.state + (size_t)(mf + chunk) * (4 * kThreads);
-                    st[pix] = p.T;
-                    st[kThreads + pix] = p.C0;
-                    st[2 * kThreads + pix] = p.C1;
-                    st[3 * kThreads + pix] = p.C2;
-                }
-            }
-            if (STATS && sub != 0) f.n_blend = n_blend0;  // a pixel's blends count on its first lane only
-        }
-        if (inside && (nch <= 1 || sub == 0)) {
-            const size_t o = (size_t)py * W + px;
-            const size_t plane = (size_t)W * H;
-            float* img = image + 3 * tg.pix0;
-            img[o] = p.C0 + p.T * bg0;
-            img[plane + o] = p.C1 + p.T * bg1;
-            img[2 * plane + o] = p.C2 + p.T * bg2;
-            final_T[tg.pix0 + o] = p.T;
-            n_contrib[tg.pix0 + o] = p.last;
-        }
-        __syncthreads();  // LDS and s_item are reused by the next tile
-        if (tid == 0) s_item = nch <= 1 ? next_item : atomicAdd(&ws.counters[0], 1u);
-        __syncthreads();
+    __shared__ union {
+        Staged st;
+        uint32_t mask[CHUNK / 32 * kThreads];
+    } s;
+    if (blockIdx.x < mask_blocks) {
+        make_masks<CHUNK, STATS>(s.mask, blockIdx.x, mask_blocks, xy, conic_o, vals, ranges, V, ws, frag_stats);
+        return;
     }
+    const uint32_t item = blockIdx.x - mask_blocks, n_heavy = ws.counters[kCntHeavy];
+    if (item >= ws.counters[kCntTiles]) return;
+    const bool heavy = item < n_heavy;
+    const uint32_t tile = ws.order[heavy ? (int64_t)item : n_tiles - 1 - (int64_t)(item - n_heavy)];
+    const uint32_t nch = ws.nch[tile];
+    const uint32_t mf = heavy ? ws.mfirst[tile] : 0u;
+    if (heavy && is_long(ws, nch, mf)) return;
+    const uint32_t r0 = ranges[2 * tile], n = ranges[2 * tile + 1] - r0;
+    const TileGeom tg = tile_geom(V, tile);
+    const int px = tg.tx * fgd::kTile + fgb::pixel_x(threadIdx.x), py = tg.ty * fgd::kTile + fgb::pixel_y(threadIdx.x);
+    const bool inside = px < tg.W && py < tg.H;
+    PixelState p = {1.0f, 0.0f, 0.0f, 0.0f, 0u, !inside};
+    Frag f = {0, 0, 0, 0};
+    blend_batches<CHUNK, STATS>(s.st, ws, xy, conic_o, rgb_depth, vals + r0, n, heavy, nch, mf, tg, p, f);
+    if (inside) write_pixel(p, px, py, tg, bg0, bg1, bg2, image, final_T, n_contrib);
     flush_stats<STATS, 4>(f, frag_stats);
 }
 
@@ -1097,25 +965,24 @@ int chunk_of(const fg_tune* tune)
     return tune->render_batch;
 }
 
-// Mask storage is capped; chunks beyond the cap compute their masks in the
-// tile's own workgroup (same results, less parallelism).
-constexpr int64_t kMaskStoreBytes = (int64_t)256 << 20;
+// The mask store is capped; long tiles past it are walked whole by one
+// workgroup (same results, less parallelism).
+constexpr int64_t kMaskStoreBytes = (int64_t)512 << 20;
 
 size_t carve(void* base, int64_t n_tiles, int64_t cap_pairs, int chunk, bool save_state, int mask_items,
-             RenderWs* w, int64_t* max_mask_items)
+             RenderWs* w, int64_t* max_items)
 {
     const int64_t mask_bytes = (int64_t)(chunk / 32) * kThreads * 4;
     const int64_t need = 2 * ((cap_pairs + chunk - 1) / chunk) + 1;
     int64_t cap = kMaskStoreBytes / mask_bytes;
     if (mask_items > 0 && mask_items < cap) cap = mask_items;
-    *max_mask_items = need < cap ? need : cap;
-    const size_t state_bytes = save_state ? (size_t)*max_mask_items * 4 * kThreads * 4 : 0;
+    *max_items = need < cap ? need : cap;
+    const size_t state_bytes = save_state ? (size_t)*max_items * 4 * kThreads * 4 : 0;
     const size_t sched_bytes = (size_t)3 * 4 * (size_t)((n_tiles + kSchedTiles - 1) / kSchedTiles + 1);
-    const size_t sizes[8] = {(size_t)n_tiles * 4, (size_t)n_tiles * 4, (size_t)n_tiles * 4,
-                             (size_t)*max_mask_items * 4, 64, (size_t)*max_mask_items * (size_t)mask_bytes,
-                             state_bytes, sched_bytes};
-    void** dst[8] = {(void**)&w->nch, (void**)&w->mfirst, (void**)&w->order, (void**)&w->mitem,
-                     (void**)&w->counters, (void**)&w->masks, (void**)&w->state, (void**)&w->sched};
+    const size_t sizes[8] = {(size_t)n_tiles * 4, (size_t)n_tiles * 4, (size_t)n_tiles * 4, (size_t)*max_items * 4, 64,
+                             (size_t)*max_items * (size_t)mask_bytes, state_bytes, sched_bytes};
+    void** dst[8] = {(void**)&w->nch, (void**)&w->mfirst, (void**)&w->order, (void**)&w->mitem, (void**)&w->counters,
+                     (void**)&w->masks, (void**)&w->state, (void**)&w->sched};
     size_t off = 0;
     for (int i = 0; i < 8; i++) {
         if (base) *dst[i] = (char*)base + off;
@@ -1146,25 +1013,26 @@ void launch(const fg_splats* splats, const uint32_t* vals, const uint32_t* range
                            w.sched, w.mfirst, w.order);
     }
     const unsigned gp = (unsigned)(n_tiles < 65536 ? n_tiles : 65536);
-    hipLaunchKernelGGL(k_tile_prep<CHUNK>, dim3(gp), dim3(kThreads), 0, s, n_tiles, V, bg[0], bg[1], bg[2], w.nch,
-                       w.mfirst, max_mask_items, w.mitem, image, final_T, n_contrib);
+    hipLaunchKernelGGL(k_tile_prep, dim3(gp), dim3(kThreads), 0, s, n_tiles, V, bg[0], bg[1], bg[2], w,
+                       max_mask_items, image, final_T, n_contrib);
     const float2* xy = (const float2*)splats->xy;
     const float4* co = (const float4*)splats->conic_o;
     const float4* rgb = (const float4*)splats->rgb_depth;
-    const unsigned gm = (unsigned)(max_mask_items < 4096 ? (max_mask_items < 1 ? 1 : max_mask_items) : 4096);
-    const unsigned gr = (unsigned)(n_tiles < 4096 ? n_tiles : 4096);
+    const unsigned gm = (unsigned)(max_mask_items < 2048 ? (max_mask_items < 1 ? 1 : max_mask_items) : 2048);
+    const unsigned gl = (unsigned)(2 * n_tiles < 4096 ? 2 * n_tiles : 4096);
+    const unsigned gr = gm + (unsigned)n_tiles;
     if (frag_stats) {
-        hipLaunchKernelGGL((k_masks<CHUNK, true>), dim3(gm), dim3(kThreads), 0, s, xy, co, vals, ranges, V, w,
-                           frag_stats);
-        hipLaunchKernelGGL((k_render<CHUNK, true, kHeavyLanes>), dim3(gr), dim3(kThreads), 0, s, xy, co, rgb, vals, ranges, n_tiles,
-                           V, bg[0], bg[1], bg[2], w, image, final_T, n_contrib, frag_stats);
+        hipLaunchKernelGGL((k_render<CHUNK, true>), dim3(gr), dim3(kThreads), 0, s, xy, co, rgb, vals, ranges, n_tiles,
+                           V, bg[0], bg[1], bg[2], w, gm, image, final_T, n_contrib, frag_stats);
+        hipLaunchKernelGGL((k_render_long<CHUNK, true>), dim3(gl), dim3(kThreads), 0, s, xy, co, rgb, vals, ranges, V,
+                           bg[0], bg[1], bg[2], w, image, final_T, n_contrib, frag_stats);
     } else {
-        hipLaunchKernelGGL((k_masks<CHUNK, false>), dim3(gm), dim3(kThreads), 0, s, xy, co, vals, ranges, V, w,
-                           frag_stats);
         const bool timed = tune && tune->blend_events[0] && tune->blend_events[1];
         if (timed) (void)hipEventRecord((hipEvent_t)tune->blend_events[0], s);
-        hipLaunchKernelGGL((k_render<CHUNK, false, kHeavyLanes>), dim3(gr), dim3(kThreads), 0, s, xy, co, rgb, vals, ranges, n_tiles,
-                           V, bg[0], bg[1], bg[2], w, image, final_T, n_contrib, frag_stats);
+        hipLaunchKernelGGL((k_render<CHUNK, false>), dim3(gr), dim3(kThreads), 0, s, xy, co, rgb, vals, ranges, n_tiles,
+                           V, bg[0], bg[1], bg[2], w, gm, image, final_T, n_contrib, frag_stats);
+        hipLaunchKernelGGL((k_render_long<CHUNK, false>), dim3(gl), dim3(kThreads), 0, s, xy, co, rgb, vals, ranges, V,
+                           bg[0], bg[1], bg[2], w, image, final_T, n_contrib, frag_stats);
         if (timed) (void)hipEventRecord((hipEvent_t)tune->blend_events[1], s);
     }
 }
@@ -1263,7 +1131,7 @@ bool render_ws_view(const void* ws, size_t ws_bytes, const fg_camera* cam, int64
     v->nch = w.nch;
     v->mfirst = w.mfirst;
     v->mitem = w.mitem;
-    v->counters = w.counters + 2;
+    v->counters = w.counters + kCntItems;
     v->state = w.state;
     v->chunk = chunk;
     v->max_items = mi;
