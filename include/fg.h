@@ -184,10 +184,10 @@ typedef struct fg_tune {
                               records on its stream right before and right after its blend
                               kernels (k_render and k_render_long), for timing them alone */
     unsigned long long* bwd_stats; /* NULL: none; else 3 device counters that fg_render_backward
-                              adds to (the caller zeroes them): [0] gradient atomic
-                              instructions of the blend's backward (one per wave and splat
-                              with a blended pixel), [1] gradient elements those add,
-                              [2] blended fragments walked */
+                              adds to (the caller zeroes them): [0] splat gradients that the
+                              blend's backward adds to memory (one per splat and batch of a
+                              range with a blended pixel, atomically), [1] gradient elements
+                              those hold, [2] blended fragments walked */
 } fg_tune;
 
 /* ---- stage 1: traversal-free parallel filter (Sec. 3.2) ---------------- */

@@ -14,16 +14,25 @@
 //                  when the forward saved its per-chunk state, the chunks of
 //                  long ranges, each walked from the (T, colour) the forward
 //                  had after that chunk, so a long range no longer runs on
-//                  one workgroup. A conservative box per splat (pixels where
-//                  its power can reach -5.6) lets a wave pass over splats
-//                  that miss its rows. Per splat, the gradients w.r.t. its 2D
-//                  mean, conic, opacity and colour are summed over the wave
-//                  (DPP permutes) and added with one atomic per value.
+//                  one workgroup. Every 8 lanes visit the splats that reach
+//                  their own 4 x 2 pixel block (fg_blocks.h). The gradients
+//                  w.r.t. a splat's 2D mean, conic, opacity and colour are
+//                  summed over the block (DPP permutes), over the tile in
+//                  LDS, and added to memory once per splat and batch of 256.
+//                  The walk's arithmetic and its LDS adds bound it, so what
+//                  counts is how many lanes of a step hold a blended pixel:
+//                  64 lanes per splat took 2069 us for 2M Gaussians at 1080p
+//                  and 337 us for 100k at 801 x 603 (9 of 64 lanes on a blended
+//                  pixel), 8 lanes per splat 1115 and 248 us; of the 1115 about
+//                  360 are the LDS adds, 220 staging, lists and memory adds.
+//                  Measured and not taken: one reduction over both entries
+//                  (1219), the next entries' LDS reads issued early (1246).
 //   k_project_bwd  one thread per selected Gaussian: the chain from those
 //                  splat gradients to the raw parameters (SH coefficients, the
 //                  mean through the 2D mean, the Jacobian and the view
 //                  direction, log-scales and the rotation through its
 //                  normalisation, opacity logits).
+#include "fg_blocks.h"
 #include "fg_device.h"
 #include "fg_render_ws.h"
 
@@ -34,7 +43,6 @@ namespace {
 constexpr int kThreads = 256;
 constexpr int kBatch = 256;
 constexpr int kNG = 9;  // du dv dA dB dC dopacity dr dg db
-constexpr float kSkipPower = -5.6f;
 
 // exp for |x| <= 87: the library's Cody & Waite exponential (exp_neg is valid
 // for positive arguments up to 88 as well).
@@ -67,60 +75,42 @@ struct BwdView {
     int64_t max_items;        // chunk items the workspace holds (bounds *n_items)
 };
 
-// Sums over the 64 lanes of the 9 gradient components, by halving: padded to
-// 16, each lane keeps half of its components and adds its partner's half of
-// the same ones, across lane bit 5, then 4 (lane shuffles), 3 and 2 (DPP row
-// and half-row mirrors, which pair lanes that differ in that bit and hold the
-// same set); then the one component left is summed within each quad. Lane l
-// returns the total of component ((l >> 2) & 15), the same in all four lanes
-// of the quad (components 9..15 are zero). 12 shuffles and 5 DPP adds, where
-// nine separate reductions take 54 DPP steps and 9 lane reads.
-__device__ __forceinline__ float grad_reduce_scatter(const float (&g)[kNG])
+// Sums over 8 lanes of the 9 gradient components, by halving: each lane keeps
+// half of its components and adds its partner's half of the same ones, across
+// lane bits 2 (half-row mirror, which pairs lanes that differ in it and hold
+// the same set), 1 and 0 (quad permutes). Lane l ends with the totals of
+// components first_component(l) and the next one (see has_component); 10 adds
+// where nine separate sums take 27.
+__device__ __forceinline__ void reduce8(const float (&g)[kNG], float (&t)[2])
 {
     const int lane = fgd::lane_id();
-    float v[16];
+    const bool b2 = (lane & 4) != 0, b1 = (lane & 2) != 0, b0 = (lane & 1) != 0;
+    float v[5];
 #pragma unroll
-    for (int c = 0; c < 16; c++) v[c] = c < kNG ? g[c] : 0.0f;
-    float w8[8];
-    {
-        const bool hi = (lane & 32) != 0;
+    for (int i = 0; i < 5; i++) {
+        const float hi = i < 4 ? g[5 + i] : 0.0f;
+        v[i] = (b2 ? hi : g[i]) + fgd::dpp_mov<0x141>(b2 ? g[i] : hi);
+    }
+    float w[3];
 #pragma unroll
-        for (int i = 0; i < 8; i++) {
-            const float keep = hi ? v[i + 8] : v[i];
-            const float send = hi ? v[i] : v[i + 8];
-            w8[i] = keep + __shfl_xor(send, 32, fgd::kWave);
-        }
+    for (int i = 0; i < 3; i++) {
+        const float hi = i < 2 ? v[3 + i] : 0.0f;
+        w[i] = (b1 ? hi : v[i]) + fgd::dpp_mov<0x4E>(b1 ? v[i] : hi);
     }
-    float w4[4];
-    {
-        const bool hi = (lane & 16) != 0;
-#pragma unroll
-        for (int i = 0; i < 4; i++) {
-            const float keep = hi ? w8[i + 4] : w8[i];
-            const float send = hi ? w8[i] : w8[i + 4];
-            w4[i] = keep + __shfl_xor(send, 16, fgd::kWave);
-        }
-    }
-    float w2[2];
-    {
-        const bool hi = (lane & 8) != 0;  // row mirror: lane i <-> 15 - i of its row
-#pragma unroll
-        for (int i = 0; i < 2; i++) {
-            const float keep = hi ? w4[i + 2] : w4[i];
-            const float send = hi ? w4[i] : w4[i + 2];
-            w2[i] = keep + fgd::dpp_mov<0x140>(send);
-        }
-    }
-    float w1;
-    {
-        const bool hi = (lane & 4) != 0;  // half-row mirror: lane i <-> 7 - i of its half row
-        const float keep = hi ? w2[1] : w2[0];
-        const float send = hi ? w2[0] : w2[1];
-        w1 = keep + fgd::dpp_mov<0x141>(send);
-    }
-    w1 = w1 + fgd::dpp_mov<0xB1>(w1);  // quad_perm [1, 0, 3, 2]
-    w1 = w1 + fgd::dpp_mov<0x4E>(w1);  // quad_perm [2, 3, 0, 1]
-    return w1;
+    t[0] = (b0 ? w[2] : w[0]) + fgd::dpp_mov<0xB1>(b0 ? w[0] : w[2]);
+    t[1] = (b0 ? 0.0f : w[1]) + fgd::dpp_mov<0xB1>(b0 ? w[1] : 0.0f);
+}
+
+__device__ __forceinline__ int first_component(int lane) { return ((lane >> 2) & 1) * 5 + ((lane >> 1) & 1) * 3 + (lane & 1) * 2; }
+
+// Whether lane l's total k (0 or 1) is a component of its own: bits 2, 1, 0 of
+// the lane choose among {0..4 | 5..8}, then {first three | the others}, then
+// {two | one}.
+__device__ __forceinline__ bool has_component(int lane, int k)
+{
+    const int in5 = ((lane >> 1) & 1) * 3 + (lane & 1) * 2 + k;  // place in its half of 5 (the upper holds 4)
+    const int in3 = (lane & 1) * 2 + k;
+    return in3 < 3 && in5 < ((lane & 4) ? 4 : 5);
 }
 
 template <bool STATS>
@@ -138,19 +128,23 @@ __global__ __launch_bounds__(kThreads) void k_render_bwd(const float2* __restric
                                                          unsigned long long* __restrict__ stats)
 {
     unsigned long long n_frag = 0, n_instr = 0, n_elem = 0;  // STATS: this lane's counts
-    __shared__ float2 s_xy[kBatch];
-    __shared__ float4 s_co[kBatch];
-    __shared__ float4 s_rgb[kBatch];
+    __shared__ float4 s_a[kBatch];
+    __shared__ float4 s_b[kBatch];
+    __shared__ float s_c[kBatch];
     __shared__ uint32_t s_g[kBatch];
-    __shared__ uint32_t s_box[kBatch];
+    __shared__ uint32_t s_bm[kBatch];
+    __shared__ __align__(16) uint8_t s_list[fgb::kBlocks][kBatch];
+    __shared__ float s_grad[kBatch * kNG];
     __shared__ uint32_t s_max;
-    const int tid = threadIdx.x;
-    const int lx = tid % fgd::kTile, ly = tid / fgd::kTile;
+    const int tid = threadIdx.x, wave = tid / fgd::kWave;
+    const int lx = fgb::pixel_x(tid), ly = fgb::pixel_y(tid);
     const int lane = fgd::lane_id();
-    const int wy0 = (tid / fgd::kWave) * (fgd::kWave / fgd::kTile);  // first pixel row of this wave
+    const int comp = first_component(lane);
+    const bool has0 = has_component(lane, 0), has1 = has_component(lane, 1);
     const size_t plane = (size_t)W * H;
     int64_t n_chunk_items = view.n_items ? (int64_t)*view.n_items : 0;
     if (n_chunk_items > view.max_items) n_chunk_items = view.max_items;
+    for (int i = tid; i < kBatch * kNG; i += kThreads) s_grad[i] = 0.0f;
     for (int64_t item = blockIdx.x; item < n_chunk_items + n_tiles; item += gridDim.x) {
         // work item: a chunk of a long range, or a whole tile
         uint32_t tile;
@@ -188,111 +182,140 @@ __global__ __launch_bounds__(kThreads) void k_render_bwd(const float2* __restric
         // T after the walked span and the colour behind it (later splats and
         // background): from final_T for a whole tile, from the state saved
         // after the chunk (colour behind = image - colour accumulated so far)
-        float T, S0, S1, S2;
+        // Only its product with the pixel's gradient is needed.
+        float T, GS;
         if (citem < 0) {
             T = inside ? final_T[o] : 1.0f;
-            S0 = T * bg0; S1 = T * bg1; S2 = T * bg2;
+            GS = (G0 * (T * bg0) + G1 * (T * bg1)) + G2 * (T * bg2);
         } else {
-            const float* st = view.state + (size_t)citem * (4 * kThreads);
-            T = st[tid];
-            S0 = inside ? image[o] - st[kThreads + tid] : 0.0f;
-            S1 = inside ? image[plane + o] - st[2 * kThreads + tid] : 0.0f;
-            S2 = inside ? image[2 * plane + o] - st[3 * kThreads + tid] : 0.0f;
+            const float* st = view.state + (size_t)citem * (4 * kThreads) + ly * fgd::kTile + lx;
+            T = st[0];
+            GS = inside ? (G0 * (image[o] - st[kThreads]) + G1 * (image[plane + o] - st[2 * kThreads])) +
+                              G2 * (image[2 * plane + o] - st[3 * kThreads])
+                        : 0.0f;
         }
         __syncthreads();  // LDS of the previous item
         if (tid == 0) s_max = 0u;
         __syncthreads();
-        atomicMax(&s_max, last);
+        {
+            uint32_t m = last;  // one LDS atomic per wave
+#pragma unroll
+            for (int d = fgd::kWave / 2; d > 0; d >>= 1) {
+                const uint32_t x = (uint32_t)__shfl_xor((int)m, d, fgd::kWave);
+                m = x > m ? x : m;
+            }
+            if (lane == 0) atomicMax(&s_max, m);
+        }
         __syncthreads();
         // positions [0, s_max) of the range hold every blended splat
         const int64_t hi = hi_cap < (int64_t)s_max ? hi_cap : (int64_t)s_max;
         for (int64_t end = hi; end > lo; end -= kBatch) {
             const int64_t begin = end - kBatch > lo ? end - kBatch : lo;
             const int cnt = (int)(end - begin);
-            __syncthreads();
             if (tid < cnt) {
                 const uint32_t g = vals[r0 + begin + tid];
-                s_g[tid] = g;
                 const float2 mm = xy[g];
-                const float4 co = conic_o[g];
-                s_xy[tid] = mm;
-                s_co[tid] = co;
-                s_rgb[tid] = rgb_depth[g];
-                s_box[tid] = fgd::splat_box(mm, co, tx, ty, W, H);
+                const float4 co = conic_o[g], c = rgb_depth[g];
+                s_g[tid] = g;
+                s_a[tid] = fgb::stage_a(mm, co);
+                s_b[tid] = fgb::stage_b(co, c);
+                s_c[tid] = c.z;
+                s_bm[tid] = fgb::block_mask(mm, co, tx, ty, W, H);
             }
             __syncthreads();
-            uint32_t boxes = fgd::kNoBox;  // lane l: box of splat (window base) + l
-            for (int jj = cnt - 1; jj >= 0; jj--) {
-                // boxes are read 64 at a time, one per lane, and tested as
-                // scalars: a splat whose box misses the wave's rows is passed
-                // over (every pixel outside the box has power < -5.6, so it
-                // blended nowhere there)
-                const int wbase = jj & ~(fgd::kWave - 1);
-                if (jj == cnt - 1 || (jj & (fgd::kWave - 1)) == fgd::kWave - 1)
-                    boxes = wbase + lane < cnt ? s_box[wbase + lane] : fgd::kNoBox;
-                const uint32_t b = (uint32_t)__builtin_amdgcn_readlane((int)boxes, jj - wbase);
-                const int bx0 = (int)(b & 255u), bx1 = (int)((b >> 8) & 255u);
-                const int by0 = (int)((b >> 16) & 255u), by1 = (int)(b >> 24);
-                if (bx0 > bx1 || by1 < wy0 || by0 > wy0 + 3) continue;
-                const uint32_t pos = (uint32_t)(begin + jj);
-                float gr[kNG] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-                bool hit = false;
-                if (pos < last && lx >= bx0 && lx <= bx1 && ly >= by0 && ly <= by1) {
-                    const float2 m = s_xy[jj];
-                    const float4 co = s_co[jj];
-                    const float dx = m.x - fpx;
-                    const float dy = m.y - fpy;
-                    const float power = -0.5f * ((co.x * dx) * dx + (co.z * dy) * dy) - (co.y * dx) * dy;
-                    if (!(power > 0.0f || power < kSkipPower)) {
-                        const float e = fgd::exp_neg_in_range(power);  // -5.6 <= power <= 0
-                        const float araw = co.w * e;
-                        const float alpha = araw < 0.99f ? araw : 0.99f;
-                        if (alpha >= 1.0f / 255.0f) {
-                            hit = true;
-                            const float4 c = s_rgb[jj];
-                            // one division, then products: the gradients carry a
-                            // tolerance, not the forward's bit-exactness
-                            const float inv = 1.0f / (1.0f - alpha);
-                            const float Tk = T * inv;
-                            const float w = alpha * Tk;
-                            gr[6] = G0 * w;
-                            gr[7] = G1 * w;
-                            gr[8] = G2 * w;
-                            const float dLda = (G0 * (c.x * Tk - S0 * inv) + G1 * (c.y * Tk - S1 * inv)) +
-                                               G2 * (c.z * Tk - S2 * inv);
-                            S0 = S0 + c.x * w;
-                            S1 = S1 + c.y * w;
-                            S2 = S2 + c.z * w;
-                            T = Tk;
-                            if (araw < 0.99f) {
-                                const float dLdp = dLda * alpha;
-                                gr[5] = dLda * e;
-                                gr[0] = dLdp * (-(co.x * dx + co.y * dy));
-                                gr[1] = dLdp * (-(co.z * dy + co.y * dx));
-                                gr[2] = dLdp * (-0.5f * (dx * dx));
-                                gr[3] = dLdp * (-(dx * dy));
-                                gr[4] = dLdp * (-0.5f * (dy * dy));
-                            }
-                        }
-                    }
+            const int m = fgb::build_lists(s_bm, cnt, s_list + 8 * wave);
+            fgb::wave_sync();
+            const uint8_t* list = s_list[tid >> 3];
+            // back to front, two entries at a time (four took 10 % longer: 117
+            // registers): their alphas and reciprocals are computed together, then
+            // T, the colour behind and the gradients follow in order
+            for (int k = (m - 1) & ~1; k >= 0; k -= 2) {
+                const uint32_t e2 = *reinterpret_cast<const uint16_t*>(list + k);
+                float4 a[2], b[2];
+                float cb[2], e[2], alpha[2], inv[2];
+                bool hit[2];
+#pragma unroll
+                for (int u = 0; u < 2; u++) {
+                    const int j = (int)((e2 >> (8 * u)) & 255u);
+                    a[u] = s_a[j];
+                    b[u] = s_b[j];
+                    cb[u] = s_c[j];
+                    const float dx = a[u].x - fpx, dy = a[u].y - fpy;
+                    const float power = ((a[u].z * dx) * dx + (b[u].x * dy) * dy) - (a[u].w * dx) * dy;
+                    e[u] = fgd::exp_neg_in_range(power);
+                    const float araw = b[u].y * e[u];
+                    alpha[u] = araw < 0.99f ? araw : 0.99f;
+                    hit[u] = k + u < m && !(power > 0.0f || power < fgb::kSkipPower) && !(alpha[u] < 1.0f / 255.0f) &&
+                             (uint32_t)(begin + j) < last;
+                    // one division, then products: the gradients carry a
+                    // tolerance, not the forward's bit-exactness
+                    inv[u] = 1.0f / (1.0f - alpha[u]);
                 }
-                if (__ballot(hit)) {
-                    // the 9 wave sums, then one atomic instruction: the first
-                    // lane of quad k adds sum k
-                    const float tot = grad_reduce_scatter(gr);
-                    const int k = lane >> 2;
-                    const bool adds = (lane & 3) == 0 && k < kNG && tot != 0.0f;
-                    if (adds) atomicAdd(gacc + (size_t)s_g[jj] * kNG + k, tot);
-                    if (STATS) {
-                        const uint64_t am = __ballot(adds);
-                        if (lane == 0 && am != 0ull) {
-                            ++n_instr;
-                            n_elem += (unsigned long long)__popcll(am);
-                        }
+#pragma unroll
+                for (int u = 1; u >= 0; u--) {
+                    if (__ballot(hit[u]) == 0ull) continue;
+                    const int j = (int)((e2 >> (8 * u)) & 255u);
+                    // q = dL/dalpha e; per opacity: q times the exponent's derivative
+                    // by the mean, q's second moments, q, and the colour's gradient
+                    float gr[kNG] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+                    if (hit[u]) {
+                        const float dx = a[u].x - fpx, dy = a[u].y - fpy;
+                        const float Tk = T * inv[u];
+                        const float w = alpha[u] * Tk;
+                        gr[6] = G0 * w;
+                        gr[7] = G1 * w;
+                        gr[8] = G2 * w;
+                        const float Gc = (G0 * b[u].z + G1 * b[u].w) + G2 * cb[u];
+                        const float dLda = Gc * Tk - GS * inv[u];
+                        GS = GS + Gc * w;
+                        T = Tk;
+                        const float q = b[u].y * e[u] < 0.99f ? dLda * e[u] : 0.0f;
+                        const float qx = q * dx, qy = q * dy;
+                        gr[0] = q * ((a[u].z + a[u].z) * dx - a[u].w * dy);
+                        gr[1] = q * ((b[u].x + b[u].x) * dy - a[u].w * dx);
+                        gr[2] = qx * dx;
+                        gr[3] = qx * dy;
+                        gr[4] = qy * dy;
+                        gr[5] = q;
                     }
+                    // the block's sums join the splat's in LDS
+                    float t[2];
+                    reduce8(gr, t);
+                    if (has0 && t[0] != 0.0f) atomicAdd(&s_grad[j * kNG + comp], t[0]);
+                    if (has1 && t[1] != 0.0f) atomicAdd(&s_grad[j * kNG + comp + 1], t[1]);
+                    if (STATS) n_frag += hit[u] ? 1u : 0u;
                 }
-                if (STATS) n_frag += hit ? 1u : 0u;
             }
+            __syncthreads();
+            // the sums of q's moments to the gradients of mean, conic and opacity
+            // (s_a.z = -A / 2, s_b.x = -C / 2, s_b.y = opacity)
+            if (tid < cnt) {
+                float* t = s_grad + tid * kNG;
+                const float4 b = s_b[tid];
+                t[0] = b.y * t[0];
+                t[1] = b.y * t[1];
+                t[2] = b.y * (-0.5f * t[2]);
+                t[3] = b.y * -t[3];
+                t[4] = b.y * (-0.5f * t[4]);
+            }
+            __syncthreads();
+            if (STATS && tid < cnt) {
+                unsigned n = 0;
+                for (int c = 0; c < kNG; c++) n += s_grad[tid * kNG + c] != 0.0f ? 1u : 0u;
+                n_instr += n != 0u ? 1u : 0u;
+                n_elem += n;
+            }
+            if (STATS) __syncthreads();
+            // one set of sums per splat and batch to memory, consecutive lanes on
+            // consecutive components
+            for (int i = tid; i < cnt * kNG; i += kThreads) {
+                const float v = s_grad[i];
+                if (v != 0.0f) {
+                    s_grad[i] = 0.0f;
+                    atomicAdd(gacc + (size_t)s_g[i / kNG] * kNG + i % kNG, v);
+                }
+            }
+            __syncthreads();
         }
     }
     if (STATS) {
