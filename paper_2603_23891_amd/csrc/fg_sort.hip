@@ -17,21 +17,29 @@
 // Pair traffic drops from ~6 passes over 12-byte (u64 key, u32 value)
 // records to 2 passes over 8-byte records at 1080p.
 //
-// Radix pass (LSD, one digit of BITS bits, stable), three kernels:
+// Radix pass (LSD, one digit of BITS bits, stable), up to three kernels:
 //   k_hist      per 1024-item tile: digit histogram (LDS atomics) -> hist[digit][tile]
 //   k_rowscan   one workgroup per digit: exclusive scan over the tiles,
-//               digit totals
+//               digit totals (few tiles: the scatter sums the rows itself)
 //   k_scatter   per tile: stable local ranks (wave ballot match on the digit
 //               bits for all of a wave's rounds, then one pass per digit over
 //               the per-(round, wave) counts in item order), items staged
 //               through LDS in locally sorted order, then written out so that
 //               consecutive lanes write consecutive addresses.
+// What bounds a pass at a few million items is the latency of its steps and the
+// scattered writes (a tile's run of one digit is a few items), so items travel
+// as 8-byte {key, value} pairs, one store each, and a digit's output base is
+// loaded while the ranks are computed: 15.6 -> 12.4 us per 8-bit depth pass of
+// 1.5M splats and 13.6 -> 12.6 per 7-bit tile pass of 1.9M pairs against
+// separate key and value stores, 10.5 for the last depth pass, which writes
+// values alone.
 //
 // Block offsets of the emission step are exclusive sums over the per-block
 // counts of all earlier blocks. Up to 8192 blocks every block adds them up
 // itself (a few thousand L2-resident words), so no scan launch sits between
 // counting and writing; larger batches scan the counts in one workgroup
-// first.
+// first. The first blocks in depth order hold the nearest and so the largest
+// splats, whose pairs are shared among workgroups in slices.
 #include "fg_device.h"
 
 #include <algorithm>
@@ -45,6 +53,7 @@ constexpr int kWaves = kThreads / fgd::kWave;
 constexpr int kEmitIPT = 4;
 constexpr int kEmitItems = kThreads * kEmitIPT;  // 1024
 constexpr int kEmitRun = 4;                       // consecutive pairs per thread
+constexpr uint32_t kEmitSlice = 2048;             // pairs a workgroup emits at a time
 
 __device__ __forceinline__ int64_t count_of(const uint32_t* p, int64_t cap)
 {
@@ -177,6 +186,9 @@ __device__ __forceinline__ uint32_t item_splat(uint32_t i, const uint32_t* s_seg
     return (uint32_t)lo * V.cap_sel + (i - s_seg[lo]);
 }
 
+// Words of a histogram row: rows start 16-byte aligned.
+__device__ __forceinline__ int64_t row_words(int64_t n_tiles) { return (n_tiles + 3) & ~(int64_t)3; }
+
 template <int BITS>
 __device__ __forceinline__ uint64_t match_digit(uint32_t d, bool valid)
 {
@@ -202,6 +214,7 @@ struct SelInput {
     const uint32_t* tiles;
     const uint32_t* n_sel;
     uint32_t* n_items;  // selection items (written by k_hist)
+    uint32_t* n_slices;  // cleared by k_hist
     uint32_t* n_out;    // packed items (written by k_scatter)
     int64_t cap_out;
     uint32_t* status;
@@ -209,10 +222,19 @@ struct SelInput {
     int64_t n_range_words;
 };
 
+// Items of a pass: the selections (the first depth pass), {key, value} pairs,
+// or separate key and value arrays; results are pairs, separate arrays, or
+// values alone.
+enum Form { kSel, kPairs, kSplit, kValues };
+struct Items {
+    uint2* kv;      // kPairs
+    uint32_t* key;  // kSplit
+    uint32_t* val;  // kSplit, kValues
+};
+
 // Key and value of item idx of a pass (valid: the item takes part).
-template <bool SEL>
-__device__ __forceinline__ void pass_item(const uint32_t* __restrict__ kin, const uint32_t* __restrict__ vin,
-                                          const SelInput& si, const SortViews& V, const uint32_t* s_seg,
+template <int IN>
+__device__ __forceinline__ void pass_item(const Items& in, const SelInput& si, const SortViews& V, const uint32_t* s_seg,
                                           int64_t idx, int64_t n, bool want_val, bool& valid, uint32_t& k,
                                           uint32_t& v)
 {
@@ -220,25 +242,33 @@ __device__ __forceinline__ void pass_item(const uint32_t* __restrict__ kin, cons
     k = 0xFFFFFFFFu;
     v = 0u;
     if (!valid) return;
-    if constexpr (SEL) {
+    if constexpr (IN == kSel) {
         const uint32_t g = item_splat((uint32_t)idx, s_seg, V);
         valid = si.tiles[g] != 0u;
         if (valid) {
             k = __float_as_uint(si.rgb_depth[g].w);
             v = g;
         }
+    } else if constexpr (IN == kPairs) {
+        if (want_val) {
+            const uint2 e = in.kv[idx];
+            k = e.x;
+            v = e.y;
+        } else {
+            k = in.kv[idx].x;
+        }
     } else {
-        k = kin[idx];
-        if (want_val) v = vin[idx];
+        k = in.key[idx];
+        if (want_val) v = in.val[idx];
     }
 }
 
-template <int BITS, int IPT, bool SEL>
-__global__ __launch_bounds__(kThreads) void k_hist(const uint32_t* __restrict__ keys, const uint32_t* __restrict__ n_p,
-                                                   int64_t cap, int shift, uint32_t* __restrict__ hist, SelInput si,
-                                                   SortViews V)
+template <int BITS, int IPT, int IN>
+__global__ __launch_bounds__(kThreads) void k_hist(Items in, const uint32_t* __restrict__ n_p, int64_t cap, int shift,
+                                                   uint32_t* __restrict__ hist, SelInput si, SortViews V)
 {
     constexpr int R = 1 << BITS;
+    constexpr bool SEL = IN == kSel;
     __shared__ uint32_t h[R];
     __shared__ uint32_t s_seg[SEL ? kMaxViews + 1 : 1];
     int64_t n;
@@ -248,7 +278,10 @@ __global__ __launch_bounds__(kThreads) void k_hist(const uint32_t* __restrict__ 
             si.ranges[t] = 0u;
         load_segments(si.n_sel, V, s_seg);
         n = s_seg[V.n];
-        if (blockIdx.x == 0 && threadIdx.x == 0) *si.n_items = (uint32_t)n;
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            *si.n_items = (uint32_t)n;
+            *si.n_slices = 0u;
+        }
     } else {
         n = count_of(n_p, cap);
     }
@@ -261,11 +294,11 @@ __global__ __launch_bounds__(kThreads) void k_hist(const uint32_t* __restrict__ 
             const int64_t idx = tile * (kThreads * IPT) + r * kThreads + threadIdx.x;
             bool valid;
             uint32_t k, v;
-            pass_item<SEL>(keys, nullptr, si, V, s_seg, idx, n, false, valid, k, v);
+            pass_item<IN>(in, si, V, s_seg, idx, n, false, valid, k, v);
             if (valid) atomicAdd(&h[(k >> shift) & (R - 1)], 1u);
         }
         __syncthreads();
-        for (int d = threadIdx.x; d < R; d += kThreads) hist[(int64_t)d * n_tiles + tile] = h[d];
+        for (int d = threadIdx.x; d < R; d += kThreads) hist[(int64_t)d * row_words(n_tiles) + tile] = h[d];
         __syncthreads();
     }
 }
@@ -278,7 +311,7 @@ __global__ __launch_bounds__(kThreads) void k_rowscan(const uint32_t* __restrict
     __shared__ uint32_t s_wave[kWaves];
     const int64_t n = count_of(n_p, cap);
     const int64_t n_tiles = (n + (kThreads * IPT) - 1) / (kThreads * IPT);
-    uint32_t* row = hist + (int64_t)blockIdx.x * n_tiles;
+    uint32_t* row = hist + (int64_t)blockIdx.x * row_words(n_tiles);
     const int64_t per = (n_tiles + kThreads - 1) / kThreads;
     const int64_t lo = threadIdx.x * per;
     const int64_t hi = lo + per < n_tiles ? lo + per : n_tiles;
@@ -305,47 +338,66 @@ __global__ __launch_bounds__(kThreads) void k_rowscan(const uint32_t* __restrict
     if (threadIdx.x == 0) digit_total[blockIdx.x] = total;
 }
 
-template <int BITS, int IPT, bool SEL>
-__global__ __launch_bounds__(kThreads) void k_scatter(const uint32_t* __restrict__ kin, const uint32_t* __restrict__ vin,
-                                                      uint32_t* __restrict__ kout, uint32_t* __restrict__ vout,
-                                                      const uint32_t* __restrict__ n_p, int64_t cap, int shift,
-                                                      const uint32_t* __restrict__ hist,
+template <int BITS, int IPT, int IN, int OUT, bool SUM>
+__global__ __launch_bounds__(kThreads) void k_scatter(Items in, Items out, const uint32_t* __restrict__ n_p,
+                                                      int64_t cap, int shift, const uint32_t* __restrict__ hist,
                                                       const uint32_t* __restrict__ digit_total, SelInput si,
                                                       SortViews V)
 {
     constexpr int R = 1 << BITS;
+    constexpr bool SEL = IN == kSel;
     static_assert(R <= kThreads, "one thread per digit");
-    __shared__ uint32_t s_base[R];
+    __shared__ uint32_t s_dst[R];    // output index of the digit's first item of this tile, less s_start
     __shared__ uint32_t s_start[R];
     // per (round, wave, digit): the group's count, then its exclusive offset
     // among the tile's items of that digit (at most (kThreads * IPT): fits 16 bits)
     __shared__ uint16_t s_cnt[IPT][kWaves][R];
-    __shared__ uint32_t s_keys[(kThreads * IPT)];
-    __shared__ uint32_t s_vals[(kThreads * IPT)];
+    __shared__ uint2 s_kv[(kThreads * IPT)];
     __shared__ uint32_t s_wave[kWaves];
     __shared__ uint32_t s_seg[SEL ? kMaxViews + 1 : 1];
     const int64_t n = count_of(n_p, cap);
     const int64_t n_tiles = (n + (kThreads * IPT) - 1) / (kThreads * IPT);
     const int tid = threadIdx.x;
     const int wave = tid / fgd::kWave;
+    const uint32_t* row = hist + (int64_t)(tid < R ? tid : 0) * row_words(n_tiles);
     if constexpr (SEL) load_segments(si.n_sel, V, s_seg);
-    {
+    uint32_t base = 0;  // output index of the digit's first item
+    auto set_base = [&](uint32_t v) {
         uint32_t tot;
-        const uint32_t v = tid < R ? digit_total[tid] : 0u;
-        const uint32_t e = block_excl_scan(v, s_wave, tot);
-        if (tid < R) s_base[tid] = e;
+        base = block_excl_scan(tid < R ? v : 0u, s_wave, tot);
         if (SEL && blockIdx.x == 0 && tid == 0) {
             *si.n_out = tot;
             if ((int64_t)tot > si.cap_out) atomicOr(si.status, FG_STATUS_ITEM_OVERFLOW);
         }
-    }
+    };
+    if constexpr (!SUM) set_base(tid < R ? digit_total[tid] : 0u);
+    else if (n_tiles == 0) set_base(0u);
     for (int64_t tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
         uint32_t k[IPT], v[IPT], below[IPT];
         bool ok[IPT];
 #pragma unroll
         for (int r = 0; r < IPT; r++) {
             const int64_t idx = tile * (kThreads * IPT) + r * kThreads + tid;
-            pass_item<SEL>(kin, vin, si, V, s_seg, idx, n, true, ok[r], k[r], v[r]);
+            pass_item<IN>(in, si, V, s_seg, idx, n, true, ok[r], k[r], v[r]);
+        }
+        // the digit's items in earlier tiles
+        uint32_t before = 0;
+        if constexpr (!SUM) {
+            if (tid < R) before = row[tile];
+        } else {
+            uint32_t all = 0;
+            if (tid < R) {
+                for (int64_t t = 0; t < n_tiles; t += 4) {
+                    const uint4 c4 = *reinterpret_cast<const uint4*>(row + t);
+                    const uint32_t c[4] = {c4.x, c4.y, c4.z, c4.w};
+#pragma unroll
+                    for (int u = 0; u < 4; u++) {
+                        all += t + u < n_tiles ? c[u] : 0u;
+                        before += t + u < tile ? c[u] : 0u;
+                    }
+                }
+            }
+            set_base(all);
         }
         {
             uint32_t* c32 = reinterpret_cast<uint32_t*>(&s_cnt[0][0][0]);
@@ -377,7 +429,10 @@ __global__ __launch_bounds__(kThreads) void k_scatter(const uint32_t* __restrict
         uint32_t cnt;  // items of this tile that take part
         {
             const uint32_t e = block_excl_scan(run, s_wave, cnt);
-            if (tid < R) s_start[tid] = e;
+            if (tid < R) {
+                s_start[tid] = e;
+                s_dst[tid] = base + before - e;
+            }
         }
         __syncthreads();
 #pragma unroll
@@ -385,8 +440,7 @@ __global__ __launch_bounds__(kThreads) void k_scatter(const uint32_t* __restrict
             if (ok[r]) {
                 const uint32_t d = (k[r] >> shift) & (R - 1);
                 const uint32_t pos = s_start[d] + s_cnt[r][wave][d] + below[r];
-                s_keys[pos] = k[r];
-                s_vals[pos] = v[r];
+                s_kv[pos] = make_uint2(k[r], v[r]);
             }
         }
         __syncthreads();
@@ -394,12 +448,15 @@ __global__ __launch_bounds__(kThreads) void k_scatter(const uint32_t* __restrict
         for (int r = 0; r < IPT; r++) {
             const int p = r * kThreads + tid;
             if ((uint32_t)p < cnt) {
-                const uint32_t key = s_keys[p];
-                const uint32_t d = (key >> shift) & (R - 1);
-                const int64_t g = (int64_t)s_base[d] + hist[(int64_t)d * n_tiles + tile] + (p - s_start[d]);
+                const uint2 e = s_kv[p];
+                const int64_t g = (int64_t)(s_dst[(e.x >> shift) & (R - 1)] + (uint32_t)p);
                 if (!SEL || g < si.cap_out) {
-                    kout[g] = key;
-                    vout[g] = s_vals[p];
+                    if constexpr (OUT == kPairs) {
+                        out.kv[g] = e;
+                    } else {
+                        if constexpr (OUT == kSplit) out.key[g] = e.x;
+                        out.val[g] = e.y;
+                    }
                 }
             }
         }
@@ -448,13 +505,28 @@ __global__ __launch_bounds__(kThreads) void k_block_scan(uint32_t* __restrict__ 
     }
 }
 
+// The blocks with more than kEmitSlice pairs are emitted by several workgroups:
+// the first takes their first kEmitSlice pairs, and their further slices
+// {block, slice} are listed. A block that finds the list full keeps all its
+// pairs (shared[block] = 0). One workgroup per block took 67 us per view of the
+// 20M-node scene at 3 sigma (a block of near splats holds 100 times the mean)
+// and 21 us for 100k large splats; slices of 2048 take 21 and 9 us, of 4096 23
+// and 13; where the counts are even it makes no difference.
+struct EmitSlices {
+    uint32_t* n;  // listed slices
+    uint2* list;
+    uint32_t* shared;
+    int64_t cap;
+};
+
 // Per 1024 splats in depth order: the sum of their tile counts (the areas of
 // their rectangles). The rectangles are gathered here once and stored in depth
 // order, so that the emission reads them contiguously.
 __global__ __launch_bounds__(kThreads) void k_count_reduce(const uint32_t* __restrict__ order,
                                                            const ushort4* __restrict__ rect,
                                                            const uint32_t* __restrict__ n_p, int64_t cap,
-                                                           uint32_t* __restrict__ bsum, ushort4* __restrict__ rect_d)
+                                                           uint32_t* __restrict__ bsum, ushort4* __restrict__ rect_d,
+                                                           EmitSlices sl)
 {
     __shared__ uint32_t s_wave[kWaves];
     const int64_t n = count_of(n_p, cap);
@@ -472,7 +544,21 @@ __global__ __launch_bounds__(kThreads) void k_count_reduce(const uint32_t* __res
         }
         uint32_t total;
         block_excl_scan(s, s_wave, total);
-        if (threadIdx.x == 0) bsum[blk] = total;
+        if (threadIdx.x == 0) {
+            bsum[blk] = total;
+            uint32_t share = 0u;  // the block's first workgroup emits all of it
+            if (total > kEmitSlice) {
+                const uint32_t more = (total - 1) / kEmitSlice;
+                const uint32_t at = atomicAdd(sl.n, more);
+                if ((unsigned long long)at + more <= (unsigned long long)sl.cap) {
+                    for (uint32_t k = 0; k < more; k++) sl.list[at + k] = make_uint2((uint32_t)blk, k + 1);
+                    share = 1u;
+                } else {
+                    atomicSub(sl.n, more);
+                }
+            }
+            sl.shared[blk] = share;
+        }
     }
 }
 
@@ -482,11 +568,11 @@ __global__ __launch_bounds__(kThreads) void k_count_reduce(const uint32_t* __res
 // positions k, k + 256, ...: a binary search over the offsets finds the
 // splat, and the position within its rectangle (rows, then columns) gives
 // the tile, numbered in its view's global tile ids.
+template <int OUT>
 __global__ __launch_bounds__(kThreads) void k_emit(const uint32_t* __restrict__ order,
                                                    const ushort4* __restrict__ rect_d, const uint32_t* __restrict__ n_p,
                                                    int64_t cap, BlockOffsets boff, int64_t cap_pairs,
-                                                   SortViews V, uint32_t* __restrict__ keys,
-                                                   uint32_t* __restrict__ vals)
+                                                   SortViews V, EmitSlices sl, Items out)
 {
     __shared__ uint32_t s_wave[kWaves];
     __shared__ unsigned long long s_red[kWaves];
@@ -496,7 +582,18 @@ __global__ __launch_bounds__(kThreads) void k_emit(const uint32_t* __restrict__ 
     const int64_t n = count_of(n_p, cap);
     const int64_t nblk = (n + kEmitItems - 1) / kEmitItems;
     const int tid = threadIdx.x;
-    for (int64_t blk = blockIdx.x; blk < nblk; blk += gridDim.x) {
+    const int64_t n_items = nblk + (int64_t)*sl.n;
+    for (int64_t it = blockIdx.x; it < n_items; it += gridDim.x) {
+        int64_t blk = it;
+        uint32_t first = 0, most = 0xFFFFFFFFu;  // of the block's pairs
+        if (it >= nblk) {
+            const uint2 e = sl.list[it - nblk];
+            blk = e.x;
+            first = e.y * kEmitSlice;
+            most = kEmitSlice;
+        } else if (sl.shared[blk]) {
+            most = kEmitSlice;
+        }
         const unsigned long long base = block_offset(boff, blk, s_red);
         const int64_t j0 = blk * kEmitItems + (int64_t)tid * kEmitIPT;
         uint32_t c[kEmitIPT];
@@ -524,7 +621,8 @@ __global__ __launch_bounds__(kThreads) void k_emit(const uint32_t* __restrict__ 
         // per run (the last splat k with s_off[k] <= o; splats with no tile
         // share their successor's offset and are passed over), then step
         // through the rectangle, rows then columns
-        for (uint32_t o0 = (uint32_t)tid * kEmitRun; o0 < total; o0 += (uint32_t)kThreads * kEmitRun) {
+        const uint32_t last = total - first < most ? total : first + most;
+        for (uint32_t o0 = first + (uint32_t)tid * kEmitRun; o0 < last; o0 += (uint32_t)kThreads * kEmitRun) {
             int lo = 0, hi = kEmitItems;
             while (hi - lo > 1) {
                 const int mid = (lo + hi) >> 1;
@@ -535,12 +633,17 @@ __global__ __launch_bounds__(kThreads) void k_emit(const uint32_t* __restrict__ 
             uint32_t gv = s_g[lo] / V.cap_sel;
             const uint32_t local = o0 - s_off[lo];
             uint32_t ty = q.y + local / w, tx = q.x + local % w;
-            const int m = total - o0 < (uint32_t)kEmitRun ? (int)(total - o0) : kEmitRun;
+            const int m = last - o0 < (uint32_t)kEmitRun ? (int)(last - o0) : kEmitRun;
             for (int r = 0; r < m; r++) {
                 const unsigned long long dst = base + o0 + (uint32_t)r;
                 if (dst < (unsigned long long)cap_pairs) {
-                    keys[dst] = V.tile_base[gv] + ty * V.Wt[gv] + tx;
-                    vals[dst] = s_g[lo];
+                    const uint2 e = make_uint2(V.tile_base[gv] + ty * V.Wt[gv] + tx, s_g[lo]);
+                    if constexpr (OUT == kPairs) {
+                        out.kv[dst] = e;
+                    } else {
+                        out.key[dst] = e.x;
+                        out.val[dst] = e.y;
+                    }
                 }
                 if (r + 1 < m && ++tx == q.z) {
                     tx = q.x;
@@ -579,14 +682,17 @@ size_t align_up(size_t x) { return (x + 255) & ~(size_t)255; }
 
 int64_t tiles_for(int64_t n) { return (n + kTileItems - 1) / kTileItems; }
 
-// Depth keys and splat ids ping-pong between buffers 0 and 1; the depth sort
-// has an even number of passes and ends in buffer 0, after which buffer 1
-// (8 bytes per splat) holds the rectangles in depth order.
+// Depth keys and splat ids ping-pong between buffers 0 and 1 as pairs; the last
+// of the four passes leaves the splat ids alone in buffer 0, after which buffer
+// 1 (8 bytes per splat) holds the rectangles in depth order.
 struct SortWs {
-    uint32_t *dkey0, *dval0, *dkey1, *dval1, *bsum, *kalt, *valt, *hist, *digit_total, *counts;
+    uint2 *d0, *d1, *alt;
+    uint32_t *bsum, *hist, *digit_total, *counts;
     ushort4* rect_d;
+    EmitSlices slices;
 };
-// counts[0]: concatenated selection items, [1]: tile-covering splats packed
+// counts[0]: concatenated selection items, [1]: tile-covering splats packed,
+// [2]: listed emission slices
 
 size_t carve(void* base, int64_t sel_items, int64_t cap_items, int64_t cap_pairs, SortWs* w)
 {
@@ -594,68 +700,90 @@ size_t carve(void* base, int64_t sel_items, int64_t cap_items, int64_t cap_pairs
     if (sel_items > most) most = sel_items;
     const int64_t ht = tiles_for(most);
     const size_t nblk_emit = (size_t)((cap_items + kEmitItems - 1) / kEmitItems + 1);
-    const size_t sizes[9] = {
-        (size_t)cap_items * 4, (size_t)cap_items * 4, (size_t)cap_items * 8, nblk_emit * 4,
-        (size_t)cap_pairs * 4, (size_t)cap_pairs * 4,
-        (size_t)256 * (size_t)(ht + 1) * 4, (size_t)256 * 4, 16};
-    uint32_t** dst[9] = {&w->dkey0, &w->dval0, &w->dkey1, &w->bsum, &w->kalt, &w->valt, &w->hist,
-                         &w->digit_total, &w->counts};
+    w->slices.cap = cap_pairs / kEmitSlice + 1;
+    const size_t sizes[9] = {(size_t)cap_items * 8, (size_t)cap_items * 8, (size_t)cap_pairs * 8, nblk_emit * 4,
+                             (size_t)256 * (size_t)(ht + 4) * 4, (size_t)256 * 4, 16, (size_t)w->slices.cap * 8,
+                             nblk_emit * 4};
+    void** dst[9] = {(void**)&w->d0, (void**)&w->d1, (void**)&w->alt, (void**)&w->bsum, (void**)&w->hist,
+                     (void**)&w->digit_total, (void**)&w->counts, (void**)&w->slices.list, (void**)&w->slices.shared};
     size_t off = 0;
     for (int i = 0; i < 9; i++) {
-        if (base) *dst[i] = (uint32_t*)((char*)base + off);
+        if (base) *dst[i] = (char*)base + off;
         off += align_up(sizes[i] + 4);
     }
     if (base) {
-        w->dval1 = w->dkey1 + cap_items;
-        w->rect_d = reinterpret_cast<ushort4*>(w->dkey1);
+        w->rect_d = reinterpret_cast<ushort4*>(w->d1);
+        w->slices.n = w->counts + 2;
     }
     return off;
 }
 
 // Items per thread of a radix pass: 4 (1024-item tiles) for one view, whose
-// counts are a few million; 16 (4096-item tiles) for a batch of views with a
-// capacity of tens of millions, where a scatter tile's 256 digit runs would
-// otherwise average four items (16-byte writes into 128-byte lines). Chosen
-// from the call's shape on the host (the counts stay on the device).
+// counts are a few million; 8 (2048-item tiles) for a batch of views with a
+// capacity of tens of millions, where a scatter tile's 256 digit runs average 8
+// items (64-byte writes). Eight views of the 20M-node scene, all passes: 4 items
+// 1062 us, 8 items 893 us, 16 items (two workgroups per CU by LDS) 1031 us; one
+// view of 1.5M splats and 1.9M pairs: 4 and 8 items within 1 %.
+// Chosen from the call's shape on the host (the counts stay on the device).
+constexpr int kBigIPT = 8;
 constexpr int64_t kBigSort = (int64_t)4 << 20;
 
 // Block counts up to which the emission kernel sums its block offsets itself
 // (see BlockOffsets): up to 8M splats at 1024 per block.
 constexpr int64_t kInlineBlocks = 8192;
 
-template <int BITS, int IPT, bool SEL>
-void radix_pass_ipt(const uint32_t* kin, const uint32_t* vin, uint32_t* kout, uint32_t* vout, const uint32_t* n_p,
-                    int64_t cap, int shift, const SortWs& w, const SelInput& si, const SortViews& V, hipStream_t s)
+// Histogram tiles up to which the scatter sums each digit's row itself instead of
+// having it scanned first: every workgroup reads all rows (up to 256 KiB,
+// L2-resident), which grows with the square of the tiles, but saves a launch of
+// 3 us and its gap per pass. 15k splats, depth passes: 19 us of scatters and 12 of
+// scans before, 25 us with the sums inside (first frame pass included).
+constexpr int64_t kSumTiles = 256;
+
+template <int BITS, int IPT, int IN, int OUT>
+void radix_pass_ipt(const Items& in, const Items& out, const uint32_t* n_p, int64_t cap, int shift, const SortWs& w,
+                    const SelInput& si, const SortViews& V, hipStream_t s)
 {
-    int64_t grid = (cap + kThreads * IPT - 1) / (kThreads * IPT);
-    if (grid > 4096) grid = 4096;
-    if (grid < 1) grid = 1;
-    hipLaunchKernelGGL((k_hist<BITS, IPT, SEL>), dim3((unsigned)grid), dim3(kThreads), 0, s, kin, n_p, cap, shift,
-                       w.hist, si, V);
+    const int64_t tiles = (cap + kThreads * IPT - 1) / (kThreads * IPT);
+    const unsigned grid = (unsigned)(tiles > 4096 ? 4096 : (tiles < 1 ? 1 : tiles));
+    hipLaunchKernelGGL((k_hist<BITS, IPT, IN>), dim3(grid), dim3(kThreads), 0, s, in, n_p, cap, shift, w.hist, si, V);
+    if (IPT == kIPT && tiles <= kSumTiles) {
+        hipLaunchKernelGGL((k_scatter<BITS, IPT, IN, OUT, IPT == kIPT>), dim3(grid), dim3(kThreads), 0, s, in, out, n_p,
+                           cap, shift, w.hist, w.digit_total, si, V);
+        return;
+    }
     hipLaunchKernelGGL(k_rowscan<IPT>, dim3(1u << BITS), dim3(kThreads), 0, s, n_p, cap, w.hist, w.digit_total);
-    hipLaunchKernelGGL((k_scatter<BITS, IPT, SEL>), dim3((unsigned)grid), dim3(kThreads), 0, s, kin, vin, kout, vout,
-                       n_p, cap, shift, w.hist, w.digit_total, si, V);
+    hipLaunchKernelGGL((k_scatter<BITS, IPT, IN, OUT, false>), dim3(grid), dim3(kThreads), 0, s, in, out, n_p, cap,
+                       shift, w.hist, w.digit_total, si, V);
 }
 
-template <int BITS, bool SEL = false>
-void radix_pass(const uint32_t* kin, const uint32_t* vin, uint32_t* kout, uint32_t* vout, const uint32_t* n_p,
-                int64_t cap, int shift, bool big, const SortWs& w, const SelInput& si, const SortViews& V,
-                hipStream_t s)
+template <int BITS, int IN, int OUT>
+void radix_pass(const Items& in, const Items& out, const uint32_t* n_p, int64_t cap, int shift, bool big,
+                const SortWs& w, const SelInput& si, const SortViews& V, hipStream_t s)
 {
-    if (big) radix_pass_ipt<BITS, 16, SEL>(kin, vin, kout, vout, n_p, cap, shift, w, si, V, s);
-    else radix_pass_ipt<BITS, 4, SEL>(kin, vin, kout, vout, n_p, cap, shift, w, si, V, s);
+    if (big) radix_pass_ipt<BITS, kBigIPT, IN, OUT>(in, out, n_p, cap, shift, w, si, V, s);
+    else radix_pass_ipt<BITS, kIPT, IN, OUT>(in, out, n_p, cap, shift, w, si, V, s);
 }
 
-void radix_pass_bits(int bits, const uint32_t* kin, const uint32_t* vin, uint32_t* kout, uint32_t* vout,
-                     const uint32_t* n_p, int64_t cap, int shift, bool big, const SortWs& w, const SelInput& si,
-                     const SortViews& V, hipStream_t s)
+// A pass over the Gaussian-tile pairs: the last one and every second before it
+// write the separate output arrays, the others the pair buffer.
+template <int BITS>
+void tile_pass(bool to_split, const Items& split, const Items& alt, const uint32_t* n_p, int64_t cap, int shift,
+               bool big, const SortWs& w, const SortViews& V, hipStream_t s)
+{
+    const SelInput none{};
+    if (to_split) radix_pass<BITS, kPairs, kSplit>(alt, split, n_p, cap, shift, big, w, none, V, s);
+    else radix_pass<BITS, kSplit, kPairs>(split, alt, n_p, cap, shift, big, w, none, V, s);
+}
+
+void tile_pass_bits(int bits, bool to_split, const Items& split, const Items& alt, const uint32_t* n_p, int64_t cap,
+                    int shift, bool big, const SortWs& w, const SortViews& V, hipStream_t s)
 {
     switch (bits) {
-        case 4: radix_pass<4>(kin, vin, kout, vout, n_p, cap, shift, big, w, si, V, s); break;
-        case 5: radix_pass<5>(kin, vin, kout, vout, n_p, cap, shift, big, w, si, V, s); break;
-        case 6: radix_pass<6>(kin, vin, kout, vout, n_p, cap, shift, big, w, si, V, s); break;
-        case 7: radix_pass<7>(kin, vin, kout, vout, n_p, cap, shift, big, w, si, V, s); break;
-        default: radix_pass<8>(kin, vin, kout, vout, n_p, cap, shift, big, w, si, V, s); break;
+        case 4: tile_pass<4>(to_split, split, alt, n_p, cap, shift, big, w, V, s); break;
+        case 5: tile_pass<5>(to_split, split, alt, n_p, cap, shift, big, w, V, s); break;
+        case 6: tile_pass<6>(to_split, split, alt, n_p, cap, shift, big, w, V, s); break;
+        case 7: tile_pass<7>(to_split, split, alt, n_p, cap, shift, big, w, V, s); break;
+        default: tile_pass<8>(to_split, split, alt, n_p, cap, shift, big, w, V, s); break;
     }
 }
 
@@ -728,20 +856,20 @@ extern "C" int fg_sort(const fg_splats* splats, const uint32_t* n_sel, int64_t c
     };
     const int64_t sel_items = cap_sel * n_views;
     const bool big_depth = n_views > 1 && cap_items >= kBigSort;
-    const SelInput sel{(const float4*)splats->rgb_depth, splats->tiles, n_sel, w.counts, w.counts + 1, cap_items,
+    const SelInput sel{(const float4*)splats->rgb_depth, splats->tiles, n_sel, w.counts, w.slices.n, w.counts + 1, cap_items,
                        status, ranges, 2 * n_tiles};
     const SelInput none{};
-    radix_pass<8, true>(nullptr, nullptr, w.dkey1, w.dval1, w.counts, sel_items, 0, big_depth, w, sel, V, s);
-    uint32_t* n_vis = w.counts + 1;
-    for (int p = 1; p < 4; p++) {
-        const bool even = (p % 2) == 0;
-        radix_pass<8>(even ? w.dkey0 : w.dkey1, even ? w.dval0 : w.dval1, even ? w.dkey1 : w.dkey0,
-                      even ? w.dval1 : w.dval0, n_vis, cap_items, 8 * p, big_depth, w, none, V, s);
-    }
+    const Items d0{w.d0, nullptr, nullptr}, d1{w.d1, nullptr, nullptr};
+    const Items order{nullptr, nullptr, reinterpret_cast<uint32_t*>(w.d0)};
+    radix_pass<8, kSel, kPairs>(Items{}, d1, w.counts, sel_items, 0, big_depth, w, sel, V, s);
+    const uint32_t* n_vis = w.counts + 1;
+    radix_pass<8, kPairs, kPairs>(d1, d0, n_vis, cap_items, 8, big_depth, w, none, V, s);
+    radix_pass<8, kPairs, kPairs>(d0, d1, n_vis, cap_items, 16, big_depth, w, none, V, s);
+    radix_pass<8, kPairs, kValues>(d1, order, n_vis, cap_items, 24, big_depth, w, none, V, s);
     // 2. tile counts in depth order and key emission
     const unsigned gv = grid_for(cap_items, kEmitItems);
-    hipLaunchKernelGGL(k_count_reduce, dim3(gv), dim3(kThreads), 0, s, w.dval0, (const ushort4*)splats->rect, n_vis,
-                       cap_items, w.bsum, w.rect_d);
+    hipLaunchKernelGGL(k_count_reduce, dim3(gv), dim3(kThreads), 0, s, order.val, (const ushort4*)splats->rect, n_vis,
+                       cap_items, w.bsum, w.rect_d, w.slices);
     const BlockOffsets boff{w.bsum, (cap_items + kEmitItems - 1) / kEmitItems <= kInlineBlocks, n_pairs, cap_pairs,
                             status, FG_STATUS_PAIR_OVERFLOW};
     if (!boff.inline_sum)
@@ -755,21 +883,20 @@ extern "C" int fg_sort(const fg_splats* splats, const uint32_t* n_sel, int64_t c
         if (bits < 4) bits = 4;
     }
     const int passes = (tile_bits + bits - 1) / bits;
-    // emit into the buffer that the last pass will not write
-    uint32_t* ek = cap_pairs == 0 ? nullptr : (passes % 2) ? w.kalt : tile_keys;
-    uint32_t* ev = cap_pairs == 0 ? nullptr : (passes % 2) ? w.valt : vals;
-    hipLaunchKernelGGL(k_emit, dim3(gv), dim3(kThreads), 0, s, w.dval0, w.rect_d, n_vis, cap_items, boff, cap_pairs,
-                       V, ek, ev);
+    // emit into the buffer that the first pass reads
+    const Items split{nullptr, tile_keys, vals}, alt{w.alt, nullptr, nullptr};
+    const unsigned ge = gv + grid_for(w.slices.cap, 4);
+    if (passes % 2)
+        hipLaunchKernelGGL(k_emit<kPairs>, dim3(ge), dim3(kThreads), 0, s, order.val, w.rect_d, n_vis, cap_items, boff,
+                           cap_pairs, V, w.slices, alt);
+    else
+        hipLaunchKernelGGL(k_emit<kSplit>, dim3(ge), dim3(kThreads), 0, s, order.val, w.rect_d, n_vis, cap_items, boff,
+                           cap_pairs, V, w.slices, split);
     if (cap_pairs > 0) {
         // 3. stable sort of the pairs by tile id
-        uint32_t *ka = ek, *va = ev, *kb = (ek == tile_keys) ? w.kalt : tile_keys, *vb = (ev == vals) ? w.valt : vals;
-        for (int p = 0; p < passes; p++) {
-            radix_pass_bits(bits, ka, va, kb, vb, n_pairs, cap_pairs, bits * p, n_views > 1 && cap_pairs >= kBigSort,
-                            w, none, V, s);
-            uint32_t* t;
-            t = ka; ka = kb; kb = t;
-            t = va; va = vb; vb = t;
-        }
+        for (int p = 0; p < passes; p++)
+            tile_pass_bits(bits, (passes - p) % 2 != 0, split, alt, n_pairs, cap_pairs, bits * p,
+                           n_views > 1 && cap_pairs >= kBigSort, w, V, s);
         hipLaunchKernelGGL(k_ranges, dim3(grid_for(cap_pairs, 256)), dim3(256), 0, s, tile_keys, n_pairs, cap_pairs,
                            cams[0].tile_base, n_tiles, ranges);
     }
