@@ -109,7 +109,56 @@ __device__ __forceinline__ bool box_outside(const fgd::Cam& c, float4 lo, float4
     return false;
 }
 
+// A pass over 8 views keeps the small and blocked bits of a node as one byte
+// (bit v: view v), other passes as one bit plane per view; both take the same
+// space. An ancestor step or a child's lookup of 8 views is then one load
+// instead of 8 in as many cache lines: on the 20M-node scene k_blocked took 117
+// us and takes 60. Fewer views would need more space than their planes.
+template <int NV, bool BYTES>
+__device__ __forceinline__ uint32_t view_bits(const uint32_t* __restrict__ bits, int64_t words, int nv, int64_t n)
+{
+    if constexpr (BYTES) return reinterpret_cast<const uint8_t*>(bits)[n];
+    uint32_t b = 0;
+#pragma unroll
+    for (int v = 0; v < NV; v++)
+        if (v < nv && bit_of(bits + v * words, n)) b |= 1u << v;
+    return b;
+}
+
+// Stores the bits of this thread's node n (below limit); all lanes take part.
+template <int NV, bool BYTES>
+__device__ __forceinline__ void store_view_bits(uint32_t* __restrict__ bits, int64_t words, int nv, int64_t n,
+                                                int64_t limit, uint32_t b)
+{
+    if constexpr (BYTES) {
+        if (n < limit) reinterpret_cast<uint8_t*>(bits)[n] = (uint8_t)b;
+        return;
+    }
+    const int64_t base = n - (int64_t)fgd::lane_id();
+#pragma unroll
+    for (int v = 0; v < NV; v++)
+        if (v < nv) store_wave_bits(bits + v * words, base, limit, __ballot((b >> v) & 1u));
+}
+
+// Views (bits) whose frustum a box may meet; all of them without boxes.
 template <int NV>
+__device__ __forceinline__ uint32_t views_of_tile(const float4* __restrict__ tile_box, int64_t tile, const CamSet& cams,
+                                                  const fg_camera* __restrict__ dcams, int nv)
+{
+    uint32_t in = (1u << nv) - 1u;
+    if (!tile_box) return in;
+    const float4 lo = tile_box[2 * tile], hi = tile_box[2 * tile + 1];
+#pragma unroll
+    for (int v = 0; v < NV; v++) {
+        if (v >= nv) break;
+        fgd::Cam cam = cams.c[v];
+        if (dcams) fgd::pose_from(cam, dcams + v);
+        if (box_outside(cam, lo, hi)) in &= ~(1u << v);
+    }
+    return in;
+}
+
+template <int NV, bool BYTES>
 __global__ __launch_bounds__(kBlock) void k_small(const float* __restrict__ mean, const float* __restrict__ scale,
                                                   const float* __restrict__ quat, const uint8_t* __restrict__ flags,
                                                   int64_t N, int64_t span, CamSet cams,
@@ -159,12 +208,7 @@ __global__ __launch_bounds__(kBlock) void k_small(const float* __restrict__ mean
             }
         }
     }
-    const int64_t base = n - (int64_t)fgd::lane_id();
-#pragma unroll
-    for (int v = 0; v < NV; v++) {
-        if (v >= nv) break;
-        store_wave_bits(small_bits + v * words, base, span, __ballot((small >> v) & 1u));
-    }
+    store_view_bits<NV, BYTES>(small_bits, words, nv, n, span, small);
 }
 
 // Whether the ancestor walks of k_blocked workgroup blockIdx.x can be left
@@ -184,21 +228,12 @@ __device__ __forceinline__ bool skip_walks(const float4* __restrict__ tile_box, 
     if (cr.x > cr.y) return true;
     const int64_t t0 = cr.x / kTileNodes, t1 = cr.y / kTileNodes;
     if (t1 - t0 >= 8) return false;
-    bool out = true;
-    for (int64_t t = t0; t <= t1 && out; t++) {
-        const float4 lo = tile_box[2 * t], hi = tile_box[2 * t + 1];
-#pragma unroll
-        for (int v = 0; v < NV; v++) {
-            if (v >= nv) break;
-            fgd::Cam cam = cams.c[v];
-            if (dcams) fgd::pose_from(cam, dcams + v);
-            out = out && box_outside(cam, lo, hi);
-        }
-    }
-    return out;
+    for (int64_t t = t0; t <= t1; t++)
+        if (views_of_tile<NV>(tile_box, t, cams, dcams, nv) != 0u) return false;
+    return true;
 }
 
-template <int NV>
+template <int NV, bool BYTES>
 __global__ __launch_bounds__(kBlock) void k_blocked(const int32_t* __restrict__ parent, const uint8_t* __restrict__ flags,
                                                     const uint32_t* __restrict__ small_bits, int64_t words,
                                                     int64_t span, int max_depth, int nv,
@@ -208,10 +243,7 @@ __global__ __launch_bounds__(kBlock) void k_blocked(const int32_t* __restrict__ 
 {
     const int64_t n = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (skip_walks<NV>(tile_box, crange, cams, dcams, nv)) {
-        const int64_t base = n - (int64_t)fgd::lane_id();
-#pragma unroll
-        for (int v = 0; v < NV; v++)
-            if (v < nv) store_wave_bits(blocked_bits + v * words, base, span, 0ull);
+        store_view_bits<NV, BYTES>(blocked_bits, words, nv, n, span, 0u);
         return;
     }
     const uint32_t all = (1u << nv) - 1u;
@@ -221,28 +253,19 @@ __global__ __launch_bounds__(kBlock) void k_blocked(const int32_t* __restrict__ 
         int64_t a = n;
         int32_t p = parent[n];
         int hops = 0;
-#pragma unroll
-        for (int v = 0; v < NV; v++)
-            if (v < nv && bit_of(small_bits + v * words, n)) blocked |= 1u << v;
+        blocked = view_bits<NV, BYTES>(small_bits, words, nv, n);
         while (blocked != all && p >= 0) {
             if ((int64_t)p >= a || (int64_t)p >= span || hops >= max_depth) {
                 bad = true;
                 break;
             }
-#pragma unroll
-            for (int v = 0; v < NV; v++)
-                if (v < nv && bit_of(small_bits + v * words, p)) blocked |= 1u << v;
+            blocked |= view_bits<NV, BYTES>(small_bits, words, nv, p);
             a = p;
             p = parent[p];
             ++hops;
         }
     }
-    const int64_t base = n - (int64_t)fgd::lane_id();
-#pragma unroll
-    for (int v = 0; v < NV; v++) {
-        if (v >= nv) break;
-        store_wave_bits(blocked_bits + v * words, base, span, __ballot((blocked >> v) & 1u));
-    }
+    store_view_bits<NV, BYTES>(blocked_bits, words, nv, n, span, blocked);
     if (__ballot(bad) && fgd::lane_id() == 0) atomicOr(status, FG_STATUS_BAD_PARENT);
 }
 
@@ -362,7 +385,7 @@ __global__ __launch_bounds__(kBlock) void k_chain_check(const int32_t* __restric
     if (__ballot(bad) && fgd::lane_id() == 0) crange[blockIdx.x] = make_int2(-1, -1);
 }
 
-template <int NV>
+template <int NV, bool BYTES>
 __global__ __launch_bounds__(kBlock) void k_select(const float* __restrict__ mean, const int32_t* __restrict__ parent,
                                                    const uint8_t* __restrict__ flags,
                                                    const uint32_t* __restrict__ small_bits,
@@ -379,31 +402,23 @@ __global__ __launch_bounds__(kBlock) void k_select(const float* __restrict__ mea
     const int wave = tid / fgd::kWave;
     const int64_t tile = blockIdx.x;
     const uint32_t all = (1u << nv) - 1u;
-    // A tile whose box lies outside every view's frustum selects nothing
+    // A tile whose box lies outside a view's frustum selects nothing in it
     // (R&L needs F: a leaf in the frustum, an internal node small, which
-    // includes being in the frustum): its selection words and count are
-    // zero, and none of its nodes is read.
-    if (tile_box) {
-        const float4 lo = tile_box[2 * tile], hi = tile_box[2 * tile + 1];
-        bool out = true;
+    // includes being in the frustum): the selection words and count are zero,
+    // and where that holds for all views none of its nodes is read. With 8
+    // views of the 20M-node scene this and the byte layout took the kernel from
+    // 252 us to 140.
+    const uint32_t in = views_of_tile<NV>(tile_box, tile, cams, dcams, nv);
+    if (in == 0u) {
 #pragma unroll
-        for (int v = 0; v < NV; v++) {
-            if (v >= nv) break;
-            fgd::Cam cam = cams.c[v];
-            if (dcams) fgd::pose_from(cam, dcams + v);
-            out = out && box_outside(cam, lo, hi);
+        for (int r = 0; r < kRounds; r++) {
+            const int64_t n = tile * kTileNodes + r * kBlock + tid;
+#pragma unroll
+            for (int v = 0; v < NV; v++)
+                if (v < nv) store_wave_bits(sel_bits + v * sel_words, n - (int64_t)fgd::lane_id(), N, 0ull);
         }
-        if (out) {
-#pragma unroll
-            for (int r = 0; r < kRounds; r++) {
-                const int64_t n = tile * kTileNodes + r * kBlock + tid;
-#pragma unroll
-                for (int v = 0; v < NV; v++)
-                    if (v < nv) store_wave_bits(sel_bits + v * sel_words, n - (int64_t)fgd::lane_id(), N, 0ull);
-            }
-            if (tid < nv) tile_cnt[(int64_t)tid * n_tiles + tile] = 0u;
-            return;
-        }
+        if (tid < nv) tile_cnt[(int64_t)tid * n_tiles + tile] = 0u;
+        return;
     }
     bool bad = false;
     // Loads are issued phase by phase for all rounds at once (parent links and
@@ -430,9 +445,7 @@ __global__ __launch_bounds__(kBlock) void k_select(const float* __restrict__ mea
                 bad = true;
                 cull[r] = all;
             } else {
-#pragma unroll
-                for (int v = 0; v < NV; v++)
-                    if (v < nv && bit_of(blocked_bits + v * words, p)) cull[r] |= 1u << v;
+                cull[r] = view_bits<NV, BYTES>(blocked_bits, words, nv, p);
             }
         }
     }
@@ -441,36 +454,67 @@ __global__ __launch_bounds__(kBlock) void k_select(const float* __restrict__ mea
     for (int r = 0; r < kRounds; r++) {
         const int64_t n = tile * kTileNodes + r * kBlock + tid;
         mx[r] = my[r] = mz[r] = 0.0f;
-        if (n < N && cull[r] != all && (fl[r] & 1u)) {
+        if (n < N && (in & ~cull[r]) != 0u && (fl[r] & 1u)) {
             mx[r] = __builtin_nontemporal_load(mean + n);
             my[r] = __builtin_nontemporal_load(mean + N + n);
             mz[r] = __builtin_nontemporal_load(mean + 2 * N + n);
         }
     }
+    // internal nodes: RL = small (as bytes loaded once for all views)
+    uint32_t small[kRounds];
+    if constexpr (BYTES) {
+#pragma unroll
+        for (int r = 0; r < kRounds; r++) {
+            const int64_t n = tile * kTileNodes + r * kBlock + tid;
+            small[r] = n < N && !(fl[r] & 1u) && (in & ~cull[r]) != 0u ? view_bits<NV, BYTES>(small_bits, words, nv, n) : 0u;
+        }
+    }
     uint32_t cnt[NV];
 #pragma unroll
     for (int v = 0; v < NV; v++) cnt[v] = 0u;
-#pragma unroll
-    for (int r = 0; r < kRounds; r++) {
+    auto select = [&](int r, int v, const fgd::Cam& cam) {
         const int64_t n = tile * kTileNodes + r * kBlock + tid;
+        bool sel = false;
+        if (n < N && !((cull[r] >> v) & 1u)) {
+            if (fl[r] & 1u) {  // leaf: RL = in frustum
+                float x, y, z;
+                fgd::to_camera(cam, mx[r], my[r], mz[r], x, y, z);
+                sel = fgd::in_frustum(cam, x, y, z);
+            } else if constexpr (BYTES) {  // internal: RL = small
+                sel = (small[r] >> v) & 1u;
+            } else {
+                sel = bit_of(small_bits + v * words, n);
+            }
+        }
+        return __ballot(sel);
+    };
+    if constexpr (NV == 1) {
+        fgd::Cam cam = cams.c[0];
+        if (dcams) fgd::pose_from(cam, dcams);
 #pragma unroll
-        for (int v = 0; v < NV; v++) {
-            if (v >= nv) break;
-            bool sel = false;
-            if (n < N && !((cull[r] >> v) & 1u)) {
-                if (fl[r] & 1u) {  // leaf: RL = in frustum
+        for (int r = 0; r < kRounds; r++) {
+            const uint64_t ball = select(r, 0, cam);
+            store_wave_bits(sel_bits, tile * kTileNodes + r * kBlock + (tid - fgd::lane_id()), N, ball);
+            cnt[0] += (uint32_t)__popcll(ball);
+        }
+    } else {
+        // node by node: view by view would keep 8 rounds' positions live (100
+        // registers instead of 72) and took 169 us instead of 138
+#pragma unroll
+        for (int r = 0; r < kRounds; r++) {
+#pragma unroll
+            for (int v = 0; v < NV; v++) {
+                if (v >= nv) break;
+                uint64_t ball = 0ull;
+                if ((in >> v) & 1u) {
                     fgd::Cam cam = cams.c[v];
                     if (dcams) fgd::pose_from(cam, dcams + v);
-                    float x, y, z;
-                    fgd::to_camera(cam, mx[r], my[r], mz[r], x, y, z);
-                    sel = fgd::in_frustum(cam, x, y, z);
-                } else {  // internal: RL = small
-                    sel = bit_of(small_bits + v * words, n);
+                    ball = select(r, v, cam);
+                    cnt[v] += (uint32_t)__popcll(ball);
                 }
+                store_wave_bits(sel_bits + v * sel_words, tile * kTileNodes + r * kBlock + (tid - fgd::lane_id()), N,
+                                ball);
             }
-            const uint64_t ball = __ballot(sel);
-            store_wave_bits(sel_bits + v * sel_words, n - (int64_t)fgd::lane_id(), N, ball);
-            cnt[v] += (uint32_t)__popcll(ball);
         }
     }
     if (__ballot(bad) && fgd::lane_id() == 0) atomicOr(status, FG_STATUS_BAD_PARENT);
@@ -584,17 +628,16 @@ __global__ __launch_bounds__(kBlock) void k_compact(const uint32_t* __restrict__
         if (lane >= d) x += y;
     }
     const uint32_t excl = tile_off[(int64_t)v * n_tiles + tile] + x - c;
-    const uint64_t lt = fgd::lanemask_lt();
     uint32_t* out = sel_idx + (int64_t)v * cap_sel;
     const uint32_t lo = (uint32_t)b, hi = (uint32_t)(b >> 32);
-#pragma unroll 4
-    for (int g = 0; g < kGroups; g++) {
-        const uint64_t gb = (uint64_t)(uint32_t)__shfl((int)lo, g, fgd::kWave) |
-                            ((uint64_t)(uint32_t)__shfl((int)hi, g, fgd::kWave) << 32);
-        if (gb == 0ull) continue;  // nothing selected in this group (the same for the whole wave)
-        const uint32_t off = (uint32_t)__shfl((int)excl, g, fgd::kWave);
-        if ((gb >> lane) & 1ull) {
-            const uint32_t o = off + (uint32_t)__popcll(gb & lt);
+#pragma unroll
+    for (int g = 0; g < kGroups; g++) {  // a group's word and offset in scalar registers (by shuffles: 67 us, now 34)
+        const uint32_t glo = (uint32_t)__builtin_amdgcn_readlane((int)lo, g);
+        const uint32_t ghi = (uint32_t)__builtin_amdgcn_readlane((int)hi, g);
+        if ((glo | ghi) == 0u) continue;  // nothing selected in this group
+        const uint32_t off = (uint32_t)__builtin_amdgcn_readlane((int)excl, g);
+        if (((lane < 32 ? glo : ghi) >> (lane & 31)) & 1u) {
+            const uint32_t o = off + __builtin_amdgcn_mbcnt_hi(ghi, __builtin_amdgcn_mbcnt_lo(glo, 0u));
             if ((int64_t)o < cap_sel) out[o] = (uint32_t)(tile * kTileNodes + (int64_t)g * fgd::kWave + lane);
         }
     }
@@ -622,7 +665,7 @@ size_t carve(void* base, int64_t N, int64_t span, int n_views, FilterWs* w)
     return off;
 }
 
-template <int NV>
+template <int NV, bool BYTES = false>
 void launch_pass(const fg_tree* tree, const CamSet& cs, const fg_camera* dcams, int nv, float tau_R,
                  uint32_t* sel_bits, int64_t sel_words,
                  uint32_t* sel_idx, int64_t cap_sel, uint32_t* n_sel, uint32_t* status, bool reset_status,
@@ -630,15 +673,15 @@ void launch_pass(const fg_tree* tree, const CamSet& cs, const fg_camera* dcams, 
 {
     if (span > 0) {
         const dim3 g((unsigned)((span + kBlock - 1) / kBlock));
-        hipLaunchKernelGGL(k_small<NV>, g, dim3(kBlock), 0, s, tree->mean, tree->scale, tree->quat, tree->flags, N,
+        hipLaunchKernelGGL((k_small<NV, BYTES>), g, dim3(kBlock), 0, s, tree->mean, tree->scale, tree->quat, tree->flags, N,
                            span, cs, dcams, nv, tau_R, w.small_bits, w.words, (const float4*)tree->tile_box, status,
                            reset_status);
         const float4* box = (const float4*)tree->tile_box;
         const int2* crange = box ? (const int2*)(box + 2 * n_tiles) : nullptr;
-        hipLaunchKernelGGL(k_blocked<NV>, g, dim3(kBlock), 0, s, tree->parent, tree->flags, w.small_bits, w.words,
+        hipLaunchKernelGGL((k_blocked<NV, BYTES>), g, dim3(kBlock), 0, s, tree->parent, tree->flags, w.small_bits, w.words,
                            span, tree->max_depth, nv, w.blocked_bits, box, crange, cs, dcams, status);
     }
-    hipLaunchKernelGGL(k_select<NV>, dim3((unsigned)n_tiles), dim3(kBlock), 0, s, tree->mean, tree->parent,
+    hipLaunchKernelGGL((k_select<NV, BYTES>), dim3((unsigned)n_tiles), dim3(kBlock), 0, s, tree->mean, tree->parent,
                        tree->flags, w.small_bits, w.blocked_bits, w.words, N, span, cs, dcams, nv, sel_bits, sel_words,
                        w.tile_cnt, n_tiles, (const float4*)tree->tile_box, status);
     hipLaunchKernelGGL(k_tile_scan, dim3((unsigned)nv), dim3(kScanThreads), 0, s, w.tile_cnt, n_tiles, n_sel,
@@ -694,7 +737,8 @@ int run_filter(const fg_tree* tree, const fg_camera* cams, int32_t n_views, cons
         if (nv == 1) launch_pass<1>(tree, cs, dc, nv, tau_R, sb, sel_words, si, cap_sel, ns, status, rs, w, N, span, n_tiles, s);
         else if (nv == 2) launch_pass<2>(tree, cs, dc, nv, tau_R, sb, sel_words, si, cap_sel, ns, status, rs, w, N, span, n_tiles, s);
         else if (nv <= 4) launch_pass<4>(tree, cs, dc, nv, tau_R, sb, sel_words, si, cap_sel, ns, status, rs, w, N, span, n_tiles, s);
-        else launch_pass<8>(tree, cs, dc, nv, tau_R, sb, sel_words, si, cap_sel, ns, status, rs, w, N, span, n_tiles, s);
+        else if (nv < 8) launch_pass<8>(tree, cs, dc, nv, tau_R, sb, sel_words, si, cap_sel, ns, status, rs, w, N, span, n_tiles, s);
+        else launch_pass<8, true>(tree, cs, dc, nv, tau_R, sb, sel_words, si, cap_sel, ns, status, rs, w, N, span, n_tiles, s);
     }
     return hipGetLastError() == hipSuccess ? FG_OK : FG_ERR_HIP;
 }
