@@ -27,7 +27,11 @@
 //                  360 are the LDS adds, 220 staging, lists and memory adds.
 //                  Measured and not taken: one reduction over both entries
 //                  (1219), the next entries' LDS reads issued early (1246).
-//   k_project_bwd  one thread per selected Gaussian: the chain from those
+//   k_bwd_init, k_bwd_map  clear the splat gradients and note each Gaussian's
+//                  selection index, so that k_project_bwd writes every
+//                  gradient once (zeros for the others) and no pass clears
+//                  them before.
+//   k_project_bwd  one thread per Gaussian, for the selected the chain from those
 //                  splat gradients to the raw parameters (SH coefficients, the
 //                  mean through the 2D mean, the Jacobian and the view
 //                  direction, log-scales and the rotation through its
@@ -57,10 +61,28 @@ __global__ void k_activate(const float* __restrict__ log_scale, const float* __r
     }
 }
 
-__global__ void k_zero(float* __restrict__ p, int64_t n)
+// Clears the splat gradients of the selected, and marks every Gaussian as not
+// selected in the map.
+__global__ __launch_bounds__(256) void k_bwd_init(const uint32_t* __restrict__ n_sel_p, int64_t cap_sel, int64_t m,
+                                                  float* __restrict__ gacc, int32_t* __restrict__ map)
 {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-        p[i] = 0.0f;
+    int64_t n_sel = (int64_t)*n_sel_p;
+    if (n_sel > cap_sel) n_sel = cap_sel;
+    const int64_t first = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, step = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t i = first; i < n_sel * kNG; i += step) gacc[i] = 0.0f;
+    for (int64_t g = first; g < m; g += step) map[g] = -1;
+}
+
+__global__ __launch_bounds__(256) void k_bwd_map(const uint32_t* __restrict__ sel_idx,
+                                                 const uint32_t* __restrict__ n_sel_p, int64_t cap_sel, int64_t m,
+                                                 int32_t* __restrict__ map)
+{
+    int64_t n_sel = (int64_t)*n_sel_p;
+    if (n_sel > cap_sel) n_sel = cap_sel;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n_sel; i += (int64_t)gridDim.x * blockDim.x) {
+        const int64_t g = sel_idx[i];
+        if (g < m) map[g] = (int32_t)i;
+    }
 }
 
 // Chunk items of long ranges (from the forward's saved state) and whole
@@ -367,16 +389,30 @@ __device__ __forceinline__ void sh_basis_and_grad(float x, float y, float z, flo
 }
 
 template <int D>
-__global__ __launch_bounds__(256) void k_project_bwd(fg_params prm, fgd::Cam cam, const uint32_t* __restrict__ sel_idx,
-                                                     const uint32_t* __restrict__ n_sel_p, int64_t cap_sel,
-                                                     const float* __restrict__ gacc, fg_grads out)
+__global__ __launch_bounds__(256) void k_project_bwd(fg_params prm, fgd::Cam cam, const float* __restrict__ gacc,
+                                                     fg_grads out)
 {
     constexpr int K = (D + 1) * (D + 1);
     const int64_t m = prm.m;
-    int64_t n_sel = (int64_t)*n_sel_p;
-    if (n_sel > cap_sel) n_sel = cap_sel;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n_sel; i += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t g = sel_idx[i];
+    for (int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; g < m; g += (int64_t)gridDim.x * blockDim.x) {
+        // the map lies in the logit gradients: this thread's own entry is read
+        // here and written below
+        const int32_t i = __float_as_int(out.logit[g]);
+        if (i < 0) {
+            for (int a = 0; a < 3; a++) out.mean[a * m + g] = 0.0f;
+            for (int a = 0; a < 3; a++) out.log_scale[a * m + g] = 0.0f;
+            for (int a = 0; a < 4; a++) out.quat[a * m + g] = 0.0f;
+            out.logit[g] = 0.0f;
+            float* zsh = out.sh + (size_t)g * (K * 3);
+            if constexpr ((K * 3) % 4 == 0) {
+#pragma unroll
+                for (int q = 0; q < K * 3 / 4; q++) reinterpret_cast<float4*>(zsh)[q] = make_float4(0.f, 0.f, 0.f, 0.f);
+            } else {
+#pragma unroll
+                for (int q = 0; q < K * 3; q++) zsh[q] = 0.0f;
+            }
+            continue;
+        }
         const float* gq = gacc + (size_t)i * kNG;
         const float gu = gq[0], gv = gq[1], gA = gq[2], gB = gq[3], gC = gq[4], go = gq[5];
         const float grgb[3] = {gq[6], gq[7], gq[8]};
@@ -567,44 +603,44 @@ extern "C" int fg_render_backward(const fg_params* p, const fg_camera* cam, cons
     if (!ws || ws_bytes < fg_render_backward_workspace_size(cap_sel)) return FG_ERR_WORKSPACE;
     hipStream_t s = (hipStream_t)stream;
     const int64_t m = p->m;
-    const int K = (p->sh_degree + 1) * (p->sh_degree + 1);
     float* gacc = (float*)ws;
-    const unsigned zb = 2048;
-    hipLaunchKernelGGL(k_zero, dim3(zb), dim3(256), 0, s, gacc, (int64_t)(cap_sel > 0 ? cap_sel : 1) * kNG);
-    hipLaunchKernelGGL(k_zero, dim3(zb), dim3(256), 0, s, out->mean, 3 * m);
-    hipLaunchKernelGGL(k_zero, dim3(zb), dim3(256), 0, s, out->log_scale, 3 * m);
-    hipLaunchKernelGGL(k_zero, dim3(zb), dim3(256), 0, s, out->quat, 4 * m);
-    hipLaunchKernelGGL(k_zero, dim3(zb), dim3(256), 0, s, out->logit, m);
-    hipLaunchKernelGGL(k_zero, dim3(zb), dim3(256), 0, s, out->sh, (int64_t)K * 3 * m);
-    if (cap_sel == 0 || m == 0) return hipGetLastError() == hipSuccess ? FG_OK : FG_ERR_HIP;
-    const int Wt = (cam->width + 15) / 16, Ht = (cam->height + 15) / 16;
-    const int64_t n_tiles = (int64_t)Wt * Ht;
-    BwdView view = {nullptr, nullptr, nullptr, nullptr, nullptr, 0, 0};
-    fgr::RenderWsView rv;
-    if (image && fgr::render_ws_view(render_ws, render_ws_bytes, cam, cap_pairs, tune, &rv))
-        view = {rv.nch, rv.mfirst, rv.mitem, rv.counters, rv.state, rv.chunk, rv.max_items};
-    int64_t gb = n_tiles + (view.n_items ? rv.max_items : 0);
-    if (gb > 8192) gb = 8192;
-    unsigned long long* stats = tune ? tune->bwd_stats : nullptr;
-    if (stats)
-        hipLaunchKernelGGL(k_render_bwd<true>, dim3((unsigned)gb), dim3(kThreads), 0, s, (const float2*)splats->xy,
-                           (const float4*)splats->conic_o, (const float4*)splats->rgb_depth, vals, ranges, cam->width,
-                           cam->height, Wt, n_tiles, bg[0], bg[1], bg[2], final_T, n_contrib, image, dL_dimage, view,
-                           gacc, stats);
-    else
-        hipLaunchKernelGGL(k_render_bwd<false>, dim3((unsigned)gb), dim3(kThreads), 0, s, (const float2*)splats->xy,
-                           (const float4*)splats->conic_o, (const float4*)splats->rgb_depth, vals, ranges, cam->width,
-                           cam->height, Wt, n_tiles, bg[0], bg[1], bg[2], final_T, n_contrib, image, dL_dimage, view,
-                           gacc, stats);
+    if (m == 0) return FG_OK;
+    auto blocks_for = [](int64_t n, int64_t most) {
+        const int64_t b = (n + 255) / 256;
+        return dim3((unsigned)(b > most ? most : (b < 1 ? 1 : b)));
+    };
+    int32_t* map = (int32_t*)out->logit;  // of each Gaussian its selection index, until k_project_bwd
+    hipLaunchKernelGGL(k_bwd_init, blocks_for(cap_sel > m ? cap_sel : m, 2048), dim3(256), 0, s, n_sel, cap_sel, m,
+                       gacc, map);
+    if (cap_sel > 0) {
+        hipLaunchKernelGGL(k_bwd_map, blocks_for(cap_sel, 2048), dim3(256), 0, s, sel_idx, n_sel, cap_sel, m, map);
+        const int Wt = (cam->width + 15) / 16, Ht = (cam->height + 15) / 16;
+        const int64_t n_tiles = (int64_t)Wt * Ht;
+        BwdView view = {nullptr, nullptr, nullptr, nullptr, nullptr, 0, 0};
+        fgr::RenderWsView rv;
+        if (image && fgr::render_ws_view(render_ws, render_ws_bytes, cam, cap_pairs, tune, &rv))
+            view = {rv.nch, rv.mfirst, rv.mitem, rv.counters, rv.state, rv.chunk, rv.max_items};
+        int64_t gb = n_tiles + (view.n_items ? rv.max_items : 0);
+        if (gb > 8192) gb = 8192;
+        unsigned long long* stats = tune ? tune->bwd_stats : nullptr;
+        if (stats)
+            hipLaunchKernelGGL(k_render_bwd<true>, dim3((unsigned)gb), dim3(kThreads), 0, s, (const float2*)splats->xy,
+                               (const float4*)splats->conic_o, (const float4*)splats->rgb_depth, vals, ranges, cam->width,
+                               cam->height, Wt, n_tiles, bg[0], bg[1], bg[2], final_T, n_contrib, image, dL_dimage, view,
+                               gacc, stats);
+        else
+            hipLaunchKernelGGL(k_render_bwd<false>, dim3((unsigned)gb), dim3(kThreads), 0, s, (const float2*)splats->xy,
+                               (const float4*)splats->conic_o, (const float4*)splats->rgb_depth, vals, ranges, cam->width,
+                               cam->height, Wt, n_tiles, bg[0], bg[1], bg[2], final_T, n_contrib, image, dL_dimage, view,
+                               gacc, stats);
+    }
     const fgd::Cam c = fgd::make_cam(*cam);
-    int64_t blocks = (cap_sel + 255) / 256;
-    if (blocks > 4096) blocks = 4096;
-    const dim3 g((unsigned)blocks), b(256);
+    const dim3 g = blocks_for(m, 8192), b(256);
     switch (p->sh_degree) {
-        case 0: hipLaunchKernelGGL(k_project_bwd<0>, g, b, 0, s, *p, c, sel_idx, n_sel, cap_sel, gacc, *out); break;
-        case 1: hipLaunchKernelGGL(k_project_bwd<1>, g, b, 0, s, *p, c, sel_idx, n_sel, cap_sel, gacc, *out); break;
-        case 2: hipLaunchKernelGGL(k_project_bwd<2>, g, b, 0, s, *p, c, sel_idx, n_sel, cap_sel, gacc, *out); break;
-        default: hipLaunchKernelGGL(k_project_bwd<3>, g, b, 0, s, *p, c, sel_idx, n_sel, cap_sel, gacc, *out); break;
+        case 0: hipLaunchKernelGGL(k_project_bwd<0>, g, b, 0, s, *p, c, gacc, *out); break;
+        case 1: hipLaunchKernelGGL(k_project_bwd<1>, g, b, 0, s, *p, c, gacc, *out); break;
+        case 2: hipLaunchKernelGGL(k_project_bwd<2>, g, b, 0, s, *p, c, gacc, *out); break;
+        default: hipLaunchKernelGGL(k_project_bwd<3>, g, b, 0, s, *p, c, gacc, *out); break;
     }
     return hipGetLastError() == hipSuccess ? FG_OK : FG_ERR_HIP;
 }
