@@ -312,30 +312,39 @@ __global__ __launch_bounds__(kThreads) void k_rowscan(const uint32_t* __restrict
     const int64_t n = count_of(n_p, cap);
     const int64_t n_tiles = (n + (kThreads * IPT) - 1) / (kThreads * IPT);
     uint32_t* row = hist + (int64_t)blockIdx.x * row_words(n_tiles);
-    const int64_t per = (n_tiles + kThreads - 1) / kThreads;
-    const int64_t lo = threadIdx.x * per;
-    const int64_t hi = lo + per < n_tiles ? lo + per : n_tiles;
-    uint32_t s = 0;
-    for (int64_t i0 = lo; i0 < hi; i0 += 4) {  // 4 independent loads per step
-        uint32_t c[4];
+    // 8 consecutive words per thread and round, loaded as two vectors (a row is
+    // 16-byte aligned and padded; its padding is not counted). Rows of 4200 words:
+    // 12.6 us with a contiguous part of the row per thread, 5.9 us this way.
+    uint32_t carry = 0;
+    for (int64_t base = 0; base < n_tiles; base += 8 * kThreads) {
+        uint32_t c[8], s = 0;
+        const int64_t i0 = base + 8 * (int64_t)threadIdx.x;
 #pragma unroll
-        for (int u = 0; u < 4; u++) c[u] = i0 + u < hi ? row[i0 + u] : 0u;
-#pragma unroll
-        for (int u = 0; u < 4; u++) s += c[u];
-    }
-    uint32_t total;
-    uint32_t run = block_excl_scan(s, s_wave, total);
-    for (int64_t i0 = lo; i0 < hi; i0 += 4) {
-        uint32_t c[4];
-#pragma unroll
-        for (int u = 0; u < 4; u++) c[u] = i0 + u < hi ? row[i0 + u] : 0u;
-#pragma unroll
-        for (int u = 0; u < 4; u++) {
-            if (i0 + u < hi) row[i0 + u] = run;
-            run += c[u];
+        for (int q = 0; q < 2; q++) {
+            const int64_t i = i0 + 4 * q;
+            const uint4 v = i < n_tiles ? *reinterpret_cast<const uint4*>(row + i) : make_uint4(0u, 0u, 0u, 0u);
+            c[4 * q] = v.x;
+            c[4 * q + 1] = i + 1 < n_tiles ? v.y : 0u;
+            c[4 * q + 2] = i + 2 < n_tiles ? v.z : 0u;
+            c[4 * q + 3] = i + 3 < n_tiles ? v.w : 0u;
         }
+#pragma unroll
+        for (int k = 0; k < 8; k++) s += c[k];
+        uint32_t total;
+        uint32_t run = carry + block_excl_scan(s, s_wave, total);
+#pragma unroll
+        for (int q = 0; q < 2; q++) {
+            uint4 o;
+            o.x = run;
+            o.y = o.x + c[4 * q];
+            o.z = o.y + c[4 * q + 1];
+            o.w = o.z + c[4 * q + 2];
+            run = o.w + c[4 * q + 3];
+            if (i0 + 4 * q < n_tiles) *reinterpret_cast<uint4*>(row + i0 + 4 * q) = o;
+        }
+        carry += total;
     }
-    if (threadIdx.x == 0) digit_total[blockIdx.x] = total;
+    if (threadIdx.x == 0) digit_total[blockIdx.x] = carry;
 }
 
 template <int BITS, int IPT, int IN, int OUT, bool SUM>
