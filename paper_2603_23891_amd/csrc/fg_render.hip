@@ -116,34 +116,63 @@ __device__ __forceinline__ bool is_long(const RenderWs& ws, uint32_t nch, uint32
     return nch >= ws.counters[kCntLongChunks] && mf + nch <= ws.counters[kCntItems];
 }
 
-// One workgroup per tile, after k_schedule: the final values of an empty
-// tile's pixels (background, T = 1, no contributor), so that the blend never
-// visits it, and the chunk item -> tile map of a heavy tile's chunks.
-__global__ __launch_bounds__(kThreads) void k_tile_prep(int64_t n_tiles, RenderViews V, float bg0, float bg1,
+// After k_schedule: the final values of an empty tile's pixels (background,
+// T = 1, no contributor), so that the blend never visits it, and the chunk item
+// -> tile map of a heavy tile's chunks. Bound by its writes: with one tile per
+// workgroup (64-byte rows) 62k empty tiles took 107 us; four side by side, 16
+// bytes per store, 63 us, what their 317 MB take at the rate of a copy. With the
+// 8160 tiles of one view that leaves too few workgroups (8.3 us, 9.3 by fours),
+// so per_wg is 4 only for the tiles of many views.
+__global__ __launch_bounds__(kThreads) void k_tile_prep(int64_t n_tiles, int per_wg, RenderViews V, float bg0, float bg1,
                                                         float bg2, RenderWs ws, int64_t max_items,
                                                         float* __restrict__ image, float* __restrict__ final_T,
                                                         uint32_t* __restrict__ n_contrib)
 {
-    for (int64_t t = blockIdx.x; t < n_tiles; t += gridDim.x) {
-        const uint32_t c = ws.nch[t];
-        if (c == 0) {
-            const TileGeom g = tile_geom(V, (uint32_t)t);
-            const int px = g.tx * fgd::kTile + (int)threadIdx.x % fgd::kTile;
-            const int py = g.ty * fgd::kTile + (int)threadIdx.x / fgd::kTile;
-            if (px < g.W && py < g.H) {
-                const size_t o = (size_t)py * g.W + px;
-                const size_t plane = (size_t)g.W * g.H;
-                float* img = image + 3 * g.pix0;
-                img[o] = bg0;
-                img[plane + o] = bg1;
-                img[2 * plane + o] = bg2;
-                final_T[g.pix0 + o] = 1.0f;
-                n_contrib[g.pix0 + o] = 0u;
+    // four consecutive tiles at a time: where they are empty, side by side and
+    // wholly inside, a thread writes four pixels of a row
+    for (int64_t t0 = per_wg * (int64_t)blockIdx.x; t0 < n_tiles; t0 += per_wg * (int64_t)gridDim.x) {
+        const int n = n_tiles - t0 < per_wg ? (int)(n_tiles - t0) : per_wg;
+        uint32_t c[4];
+#pragma unroll
+        for (int k = 0; k < 4; k++) c[k] = k < n ? ws.nch[t0 + k] : 1u;
+        if ((c[0] | c[1] | c[2] | c[3]) == 0u) {
+            const TileGeom g = tile_geom(V, (uint32_t)t0), e = tile_geom(V, (uint32_t)t0 + 3);
+            const int64_t plane = (int64_t)g.W * g.H;
+            float* img = image + 3 * g.pix0;
+            const uintptr_t at = (uintptr_t)img | (uintptr_t)(final_T + g.pix0) | (uintptr_t)(n_contrib + g.pix0);
+            if (e.pix0 == g.pix0 && e.ty == g.ty && (g.tx + 4) * fgd::kTile <= g.W && (g.ty + 1) * fgd::kTile <= g.H &&
+                g.W % 4 == 0 && at % 16 == 0) {
+                const int64_t o = (int64_t)(g.ty * fgd::kTile + (int)threadIdx.x / 16) * g.W + g.tx * fgd::kTile +
+                                  4 * ((int)threadIdx.x % 16);
+                *reinterpret_cast<float4*>(img + o) = make_float4(bg0, bg0, bg0, bg0);
+                *reinterpret_cast<float4*>(img + plane + o) = make_float4(bg1, bg1, bg1, bg1);
+                *reinterpret_cast<float4*>(img + 2 * plane + o) = make_float4(bg2, bg2, bg2, bg2);
+                *reinterpret_cast<float4*>(final_T + g.pix0 + o) = make_float4(1.0f, 1.0f, 1.0f, 1.0f);
+                *reinterpret_cast<uint4*>(n_contrib + g.pix0 + o) = make_uint4(0u, 0u, 0u, 0u);
+                continue;
             }
-        } else if (c > 1) {
-            const uint32_t mf = ws.mfirst[t];
-            for (uint32_t i = threadIdx.x; i < c; i += kThreads)
-                if ((int64_t)(mf + i) < max_items) ws.mitem[mf + i] = (uint32_t)t;
+        }
+        for (int k = 0; k < n; k++) {
+            const int64_t t = t0 + k;
+            if (c[k] == 0) {
+                const TileGeom g = tile_geom(V, (uint32_t)t);
+                const int px = g.tx * fgd::kTile + (int)threadIdx.x % fgd::kTile;
+                const int py = g.ty * fgd::kTile + (int)threadIdx.x / fgd::kTile;
+                if (px < g.W && py < g.H) {
+                    const size_t o = (size_t)py * g.W + px;
+                    const size_t plane = (size_t)g.W * g.H;
+                    float* img = image + 3 * g.pix0;
+                    img[o] = bg0;
+                    img[plane + o] = bg1;
+                    img[2 * plane + o] = bg2;
+                    final_T[g.pix0 + o] = 1.0f;
+                    n_contrib[g.pix0 + o] = 0u;
+                }
+            } else if (c[k] > 1) {
+                const uint32_t mf = ws.mfirst[t];
+                for (uint32_t i = threadIdx.x; i < c[k]; i += kThreads)
+                    if ((int64_t)(mf + i) < max_items) ws.mitem[mf + i] = (uint32_t)t;
+            }
         }
     }
 }
@@ -1012,8 +1041,10 @@ void launch(const fg_splats* splats, const uint32_t* vals, const uint32_t* range
         hipLaunchKernelGGL(k_sched_write<CHUNK>, dim3((unsigned)nb), dim3(kScanThreads), 0, s, n_tiles, w.nch,
                            w.sched, w.mfirst, w.order);
     }
-    const unsigned gp = (unsigned)(n_tiles < 65536 ? n_tiles : 65536);
-    hipLaunchKernelGGL(k_tile_prep, dim3(gp), dim3(kThreads), 0, s, n_tiles, V, bg[0], bg[1], bg[2], w,
+    const int per_wg = n_tiles <= 4 * kSchedTiles ? 1 : 4;
+    const int64_t preps = (n_tiles + per_wg - 1) / per_wg;
+    const unsigned gp = (unsigned)(preps < 65536 ? preps : 65536);
+    hipLaunchKernelGGL(k_tile_prep, dim3(gp), dim3(kThreads), 0, s, n_tiles, per_wg, V, bg[0], bg[1], bg[2], w,
                        max_mask_items, image, final_T, n_contrib);
     const float2* xy = (const float2*)splats->xy;
     const float4* co = (const float4*)splats->conic_o;
