@@ -2,8 +2,8 @@
 
 The views go through the four stages together: one node-major filter call
 (passes of up to eight views), one projection call, one sort of every view's
-Gaussian-tile pairs under global tile ids, and one blend whose persistent
-workgroups take (view, tile) work items from a single queue. The cameras'
+Gaussian-tile pairs under global tile ids, and one blend over the tiles of all
+views. The cameras'
 poses live in a device array that the filter and projection kernels read, so a
 batch captured in a HIP graph replays with new poses written into that array
 (intrinsics and image sizes are fixed at capture). ``autotune`` picks the

@@ -110,7 +110,8 @@ __device__ __forceinline__ TileGeom tile_geom(const RenderViews& V, uint32_t t)
 }
 
 // Whether a heavy tile of nch chunks (first item mf) is long: its chunks' pass
-// masks are made by k_masks. Every item must have a place in the mask store.
+// masks are made by the first workgroups of k_render. Every item must have a
+// place in the mask store.
 __device__ __forceinline__ bool is_long(const RenderWs& ws, uint32_t nch, uint32_t mf)
 {
     return nch >= ws.counters[kCntLongChunks] && mf + nch <= ws.counters[kCntItems];
