@@ -5,11 +5,11 @@
 // (Eq. (8)).
 //
 //   k_kpc       one workgroup per tile. The tile's sorted splats are staged
-//               256 at a time in LDS and listed per 4 x 2 pixel block
+//               128 at a time in LDS and listed per 4 x 2 pixel block
 //               (fg_blocks.h); every 8 lanes walk their own block's list front
 //               to back with the blend's own tests (power, alpha skip,
 //               termination), and the alpha * T of the blended fragments is
-//               summed over the block (DPP) and added to the splat's LDS slot.
+//               summed in one fixed tree (see Staged).
 //               A wave stops once its pixels have all terminated; when the
 //               whole tile has terminated the remaining pairs get 0 without
 //               being visited. The pair sums go to kpc[], their mean over the
@@ -26,7 +26,8 @@
 //
 // The transmittance chain is the blend's, in the same binary32 operations, so
 // the set of blended fragments and each alpha * T are those of the sequential
-// definition; only the summation order of a pair's terms differs.
+// definition; only the summation order of a pair's terms differs. That order is
+// fixed, so a pair's KPC is the same in every run and in both walks.
 #include "fg_blocks.h"
 #include "fg_device.h"
 #include "fg_render_ws.h"
@@ -41,15 +42,32 @@ struct Edges {
     int n;
 };
 
-// LDS of a KPC walk: 256 staged splats, their block bits, the block lists and
-// the splats' sums.
+// LDS of a KPC walk: the staged splats, their block bits, the block lists and
+// the partial sums of alpha * T. A splat's 256 terms meet in one fixed tree:
+// four pixels of a row ((0 + 1) + (2 + 3), by DPP), the four such quads of a row
+// ((0 + 1) + (2 + 3)), a wave's four rows ((0 + 1) + (2 + 3)), then the waves
+// one after another: 9 roundings. Every block writes its two quads to their own
+// places, since its neighbours reach the same splat at other steps. Adding
+// the blocks' sums to one LDS float instead took up to 34 roundings, in an order
+// that changed from run to run. The quads' places are what limits the batch:
+// 128 splats let four workgroups share a CU's LDS.
+constexpr int kBatch = 128;
+constexpr int kWaves = kThreads / fgd::kWave;
+
 struct Staged {
-    float4 a[fgb::kBatch];
-    float2 b[fgb::kBatch];  // -C / 2, opacity
-    uint32_t bm[fgb::kBatch];
-    float kpc[fgb::kBatch];
-    __align__(16) uint8_t list[fgb::kBlocks][fgb::kBatch];
+    float4 a[kBatch];
+    float2 b[kBatch];  // -C / 2, opacity
+    uint32_t bm[kBatch];
+    // [wave][row][splat]: its four quads; zero where no pixel of the quad blends it
+    float4 quad[kWaves][4][kBatch];
+    __align__(16) uint8_t list[fgb::kBlocks][kBatch];
 };
+
+__device__ __forceinline__ void clear_quads(Staged& st)
+{
+    float4* q = &st.quad[0][0][0];
+    for (int i = threadIdx.x; i < kWaves * 4 * kBatch; i += kThreads) q[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+}
 
 __device__ __forceinline__ void stage(Staged& st, int i, uint32_t g, const float2* __restrict__ xy,
                                       const float4* __restrict__ conic_o, int tx, int ty, int W, int H)
@@ -62,22 +80,23 @@ __device__ __forceinline__ void stage(Staged& st, int i, uint32_t g, const float
 }
 
 // Walks this lane's block list of m entries from transmittance T; TERM: until
-// the pixel terminates (Eq. (2)), else up to the list position last. Adds
-// each splat's alpha * T over the block's 8 pixels to its sum in LDS. Four
-// alphas (independent of T) are computed together, the T chain then runs in
-// list order.
+// the pixel terminates (Eq. (2)), else up to the list position last. Writes
+// each splat's alpha * T over the block's two quads. Four alphas (independent of
+// T) are computed together, the T chain then runs in list order.
 template <bool TERM>
 __device__ __forceinline__ void walk(Staged& st, const uint8_t* list, int m, float fpx, float fpy, uint32_t pos,
                                      uint32_t last, float& T, bool& done)
 {
     const int lane = fgd::lane_id();
+    // this lane's quad: row ((lane >> 5) << 1) + ((lane >> 2) & 1) of its wave, place (lane >> 3) & 3
+    float* quad = &st.quad[threadIdx.x / fgd::kWave][((lane >> 4) & 2) | ((lane >> 2) & 1)][0].x + ((lane >> 3) & 3);
     for (int k = 0; k < m; k += 4) {
         const uint32_t e4 = *reinterpret_cast<const uint32_t*>(list + k);
         float alpha[4];
         bool hit[4];
 #pragma unroll
         for (int u = 0; u < 4; u++) {
-            const int j = (int)((e4 >> (8 * u)) & 255u);
+            const int j = (int)((e4 >> (8 * u)) & (uint32_t)(kBatch - 1));  // past m the byte is any
             const float4 a = st.a[j];
             const float2 b = st.b[j];
             bool in_range;
@@ -97,13 +116,42 @@ __device__ __forceinline__ void walk(Staged& st, const uint8_t* list, int m, flo
                 }
             }
             if (__ballot(c != 0.0f) == 0ull) continue;
-            c += fgd::dpp_mov<0x141>(c);  // lanes l and 7 - l
-            c += fgd::dpp_mov<0x4E>(c);   // lane bit 1
-            c += fgd::dpp_mov<0xB1>(c);   // lane bit 0
-            if ((lane & 7) == 0 && c != 0.0f) atomicAdd(&st.kpc[(e4 >> (8 * u)) & 255u], c);
+            c += fgd::dpp_mov<0xB1>(c);  // lane bit 0
+            c += fgd::dpp_mov<0x4E>(c);  // lane bit 1
+            if ((lane & 3) == 0 && c != 0.0f) quad[4 * ((e4 >> (8 * u)) & (uint32_t)(kBatch - 1))] = c;
         }
         if (TERM && __ballot(!done) == 0ull) break;
     }
+}
+
+// After a wave's walk of cnt staged splats: its sum of each, left in the first
+// place of the splat's first row; the other places are zero again.
+__device__ __forceinline__ void wave_sums(Staged& st, int cnt)
+{
+    const int wave = threadIdx.x / fgd::kWave;
+    for (int j = fgd::lane_id(); j < cnt; j += fgd::kWave) {
+        if (((st.bm[j] >> (8 * wave)) & 255u) == 0u) continue;  // in none of the wave's lists
+        float r[4];
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+            const float4 q = st.quad[wave][i][j];
+            r[i] = (q.x + q.y) + (q.z + q.w);
+            if (i) st.quad[wave][i][j] = make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+        st.quad[wave][0][j] = make_float4((r[0] + r[1]) + (r[2] + r[3]), 0.f, 0.f, 0.f);
+    }
+}
+
+// The sum of splat j over the waves; its places are zero again.
+__device__ __forceinline__ float pair_sum(Staged& st, int j)
+{
+    float k = 0.0f;
+#pragma unroll
+    for (int w = 0; w < kWaves; w++) {
+        k += st.quad[w][0][j].x;
+        st.quad[w][0][j].x = 0.0f;
+    }
+    return k;
 }
 
 template <bool HIST>
@@ -128,6 +176,7 @@ __global__ __launch_bounds__(kThreads) void k_kpc(const float2* __restrict__ xy,
     // tile is then left undefined and the view is marked (acc[1] < 0)
     const bool overflow = (int64_t)*n_pairs > cap_pairs;
     double g_sum = 0.0, g_num = 0.0;  // thread 0: this workgroup's tiles
+    clear_quads(st);
     for (int64_t t = blockIdx.x; t < n_tiles; t += gridDim.x) {
         const int tx = (int)(t % Wt), ty = (int)(t / Wt);
         uint32_t lo = ranges[2 * t], hi = ranges[2 * t + 1];
@@ -144,20 +193,23 @@ __global__ __launch_bounds__(kThreads) void k_kpc(const float2* __restrict__ xy,
         bool done = !(px < W && py < H);
         float T = 1.0f;
         double my_sum = 0.0;  // this thread's share of the tile's KPC sum
-        for (uint32_t b = 0; b < n; b += kThreads) {
-            const int cnt = (int)(n - b < (uint32_t)kThreads ? n - b : (uint32_t)kThreads);
+        for (uint32_t b = 0; b < n; b += kBatch) {
+            const int cnt = (int)(n - b < (uint32_t)kBatch ? n - b : (uint32_t)kBatch);
             if (tid < cnt) stage(st, tid, vals[lo + b + tid], xy, conic_o, tx, ty, W, H);
-            st.kpc[tid] = 0.0f;
             __syncthreads();
             if (__ballot(!done) != 0ull) {
                 const int m = fgb::build_lists(st.bm, cnt, st.list + 8 * wave);
                 fgb::wave_sync();
                 walk<true>(st, st.list[tid >> 3], m, fpx, fpy, b, 0u, T, done);
+                fgb::wave_sync();
+                wave_sums(st, cnt);
             }
             __syncthreads();
-            if (tid < cnt) {
-                const float k = st.kpc[tid];
-                kpc[lo + b + tid] = k;
+            // thread t sums the tile's pairs t, t + 256, ...
+            const int j = tid - (int)(b % kThreads);
+            if (j >= 0 && j < cnt) {
+                const float k = pair_sum(st, j);
+                kpc[lo + b + j] = k;
                 my_sum += (double)k;
                 if (HIST) {
                     int bin = 0;
@@ -166,13 +218,13 @@ __global__ __launch_bounds__(kThreads) void k_kpc(const float2* __restrict__ xy,
                 }
             }
             const int alive = __syncthreads_count(!done);
-            if (alive == 0 && b + kThreads < n) {
+            if (alive == 0 && b + kBatch < n) {
                 // the whole tile has terminated: the remaining pairs contribute nothing
-                for (uint32_t k = b + kThreads + tid; k < n; k += kThreads) kpc[lo + k] = 0.0f;
+                for (uint32_t k = b + kBatch + tid; k < n; k += kThreads) kpc[lo + k] = 0.0f;
                 if (HIST && tid == 0) {
                     int bin = 0;
                     while (bin < edges.n && 0.0f >= edges.e[bin]) bin++;
-                    atomicAdd(&s_hist[bin], n - (b + kThreads));
+                    atomicAdd(&s_hist[bin], n - (b + kBatch));
                 }
                 break;
             }
@@ -206,13 +258,15 @@ __global__ __launch_bounds__(kThreads) void k_kpc(const float2* __restrict__ xy,
 // T = 1). A fragment at list position pos is blended by a pixel exactly when
 // pos is below the pixel's contributor count and it passes the skip tests,
 // so the walk needs no termination test, and a chunk does not wait for the
-// ones before it. The fragments, their alpha * T and the block sums per splat
-// are those of k_kpc, bit for bit (the transmittance chain is the blend's, in
-// the same operations); as there, the blocks' sums of a splat meet in an
-// LDS float atomic, in any order. Only the per-pair KPC is written here;
+// ones before it. The fragments, their alpha * T and each splat's sum are those
+// of k_kpc, bit for bit (the transmittance chain is the blend's, in the same
+// operations). Only the per-pair KPC is written here;
 // k_tile_gtc then sums each tile's pairs in k_kpc's order. The arithmetic of
-// the walk bounds it: with 64 lanes per splat it took 792 us per view of the
-// 20M-node scene at 1080p, with 8 lanes per splat 237 us.
+// the walk and the short lists of small batches bound it: per view of the
+// 20M-node scene at 1080p it took 792 us with 64 lanes per splat and takes 359
+// with 8 (236 with batches of 256 and each block's sum added to one LDS float,
+// whose rounding was neither bounded by 9 steps nor the same in every run;
+// batches of 64 take as long as 128, of 256 583 us).
 __global__ __launch_bounds__(kThreads) void k_kpc_items(const float2* __restrict__ xy,
                                                         const float4* __restrict__ conic_o,
                                                         const uint32_t* __restrict__ vals,
@@ -230,6 +284,7 @@ __global__ __launch_bounds__(kThreads) void k_kpc_items(const float2* __restrict
     const int wave = tid / fgd::kWave;
     const int lx = fgb::pixel_x(tid), ly = fgb::pixel_y(tid);
     if ((int64_t)*n_pairs > cap_pairs) return;  // incomplete pairs: k_tile_gtc marks the view
+    clear_quads(st);
     int64_t n_chunk_items = (int64_t)*view.counters;
     if (n_chunk_items > view.max_items) n_chunk_items = view.max_items;
     for (int64_t item = blockIdx.x; item < n_chunk_items + n_tiles; item += gridDim.x) {
@@ -278,19 +333,20 @@ __global__ __launch_bounds__(kThreads) void k_kpc_items(const float2* __restrict
         __syncthreads();
         // every blended fragment of the tile lies below s_max
         const int64_t end = hi < (int64_t)s_max ? hi : (int64_t)s_max;
-        for (int64_t b = lo; b < end; b += kThreads) {
-            const int cnt = (int)(end - b < kThreads ? end - b : kThreads);
+        for (int64_t b = lo; b < end; b += kBatch) {
+            const int cnt = (int)(end - b < kBatch ? end - b : kBatch);
             if (tid < cnt) stage(st, tid, vals[r0 + b + tid], xy, conic_o, tx, ty, W, H);
-            st.kpc[tid] = 0.0f;
             __syncthreads();
             if (b < (int64_t)wlast) {  // some pixel of this wave blends in this batch
                 const int m = fgb::build_lists(st.bm, cnt, st.list + 8 * wave);
                 fgb::wave_sync();
                 bool done = false;
                 walk<false>(st, st.list[tid >> 3], m, fpx, fpy, (uint32_t)b, last, T, done);
+                fgb::wave_sync();
+                wave_sums(st, cnt);
             }
             __syncthreads();
-            if (tid < cnt) kpc[r0 + b + tid] = st.kpc[tid];
+            if (tid < cnt) kpc[r0 + b + tid] = pair_sum(st, tid);
             __syncthreads();
         }
         // pairs behind every pixel's last blended fragment contribute nothing
