@@ -41,6 +41,7 @@
 // first. The first blocks in depth order hold the nearest and so the largest
 // splats, whose pairs are shared among workgroups in slices.
 #include "fg_device.h"
+#include "fg_slices.h"
 
 #include <algorithm>
 
@@ -214,7 +215,7 @@ struct SelInput {
     const uint32_t* tiles;
     const uint32_t* n_sel;
     uint32_t* n_items;  // selection items (written by k_hist)
-    uint32_t* n_slices;  // cleared by k_hist
+    unsigned long long* n_slices;  // cleared by k_hist
     uint32_t* n_out;    // packed items (written by k_scatter)
     int64_t cap_out;
     uint32_t* status;
@@ -280,7 +281,7 @@ __global__ __launch_bounds__(kThreads) void k_hist(Items in, const uint32_t* __r
         n = s_seg[V.n];
         if (blockIdx.x == 0 && threadIdx.x == 0) {
             *si.n_items = (uint32_t)n;
-            *si.n_slices = 0u;
+            *si.n_slices = 0ull;
         }
     } else {
         n = count_of(n_p, cap);
@@ -523,13 +524,16 @@ __global__ __launch_bounds__(kThreads) void k_block_scan(uint32_t* __restrict__ 
 
 // The blocks with more than kEmitSlice pairs are emitted by several workgroups:
 // the first takes their first kEmitSlice pairs, and their further slices
-// {block, slice} are listed. A block that finds the list full keeps all its
-// pairs (shared[block] = 0). One workgroup per block took 67 us per view of the
+// {block, slice} are listed. A block whose slices do not fit the list keeps all
+// its pairs (shared[block] = 0); that takes more pairs than cap_pairs, an
+// overflow that the call reports. See fg_slices.h for the list's rule. One workgroup per block took 67 us per view of the
 // 20M-node scene at 3 sigma (a block of near splats holds 100 times the mean)
 // and 21 us for 100k large splats; slices of 2048 take 21 and 9 us, of 4096 23
 // and 13; where the counts are even it makes no difference.
+constexpr uint32_t kNoBlock = 0xFFFFFFFFu;  // an empty entry
+
 struct EmitSlices {
-    uint32_t* n;  // listed slices
+    unsigned long long* n;  // slices asked for
     uint2* list;
     uint32_t* shared;
     int64_t cap;
@@ -545,6 +549,7 @@ __global__ __launch_bounds__(kThreads) void k_count_reduce(const uint32_t* __res
                                                            EmitSlices sl)
 {
     __shared__ uint32_t s_wave[kWaves];
+    __shared__ unsigned long long s_at;
     const int64_t n = count_of(n_p, cap);
     const int64_t nblk = (n + kEmitItems - 1) / kEmitItems;
     for (int64_t blk = blockIdx.x; blk < nblk; blk += gridDim.x) {
@@ -560,19 +565,18 @@ __global__ __launch_bounds__(kThreads) void k_count_reduce(const uint32_t* __res
         }
         uint32_t total;
         block_excl_scan(s, s_wave, total);
+        uint32_t share = 0u;  // the block's first workgroup emits all of it
+        if (total > kEmitSlice) {
+            const uint32_t more = (total - 1) / kEmitSlice;
+            if (threadIdx.x == 0) s_at = atomicAdd(sl.n, (unsigned long long)more);
+            __syncthreads();
+            const fgs::Claim c = fgs::claim(s_at, more, (uint64_t)sl.cap);
+            for (uint64_t k = c.first + threadIdx.x; k < c.last; k += kThreads)
+                sl.list[k] = c.listed ? make_uint2((uint32_t)blk, (uint32_t)(k - c.first) + 1u) : make_uint2(kNoBlock, 0u);
+            share = c.listed ? 1u : 0u;
+        }
         if (threadIdx.x == 0) {
             bsum[blk] = total;
-            uint32_t share = 0u;  // the block's first workgroup emits all of it
-            if (total > kEmitSlice) {
-                const uint32_t more = (total - 1) / kEmitSlice;
-                const uint32_t at = atomicAdd(sl.n, more);
-                if ((unsigned long long)at + more <= (unsigned long long)sl.cap) {
-                    for (uint32_t k = 0; k < more; k++) sl.list[at + k] = make_uint2((uint32_t)blk, k + 1);
-                    share = 1u;
-                } else {
-                    atomicSub(sl.n, more);
-                }
-            }
             sl.shared[blk] = share;
         }
     }
@@ -598,12 +602,13 @@ __global__ __launch_bounds__(kThreads) void k_emit(const uint32_t* __restrict__ 
     const int64_t n = count_of(n_p, cap);
     const int64_t nblk = (n + kEmitItems - 1) / kEmitItems;
     const int tid = threadIdx.x;
-    const int64_t n_items = nblk + (int64_t)*sl.n;
+    const int64_t n_items = nblk + (int64_t)fgs::entries(*sl.n, (uint64_t)sl.cap);
     for (int64_t it = blockIdx.x; it < n_items; it += gridDim.x) {
         int64_t blk = it;
         uint32_t first = 0, most = 0xFFFFFFFFu;  // of the block's pairs
         if (it >= nblk) {
             const uint2 e = sl.list[it - nblk];
+            if ((int64_t)e.x >= nblk) continue;  // an empty entry
             blk = e.x;
             first = e.y * kEmitSlice;
             most = kEmitSlice;
@@ -708,7 +713,7 @@ struct SortWs {
     EmitSlices slices;
 };
 // counts[0]: concatenated selection items, [1]: tile-covering splats packed,
-// [2]: listed emission slices
+// [2, 3]: emission slices asked for (64 bits)
 
 size_t carve(void* base, int64_t sel_items, int64_t cap_items, int64_t cap_pairs, SortWs* w)
 {
@@ -729,7 +734,7 @@ size_t carve(void* base, int64_t sel_items, int64_t cap_items, int64_t cap_pairs
     }
     if (base) {
         w->rect_d = reinterpret_cast<ushort4*>(w->d1);
-        w->slices.n = w->counts + 2;
+        w->slices.n = reinterpret_cast<unsigned long long*>(w->counts + 2);
     }
     return off;
 }
