@@ -191,7 +191,7 @@ __global__ __launch_bounds__(kThreads) void k_render_bwd(const float2* __restric
         const int px = tx * fgd::kTile + lx;
         const int py = ty * fgd::kTile + ly;
         const bool inside = px < W && py < H;
-        const uint32_t r0 = ranges[2 * tile];
+        const uint32_t r0 = ranges[2 * tile], n = ranges[2 * tile + 1] - r0;
         const float fpx = (float)px + 0.5f, fpy = (float)py + 0.5f;
         const size_t o = (size_t)py * W + px;
         const uint32_t last = inside ? n_contrib[o] : 0u;
@@ -229,8 +229,10 @@ __global__ __launch_bounds__(kThreads) void k_render_bwd(const float2* __restric
             if (lane == 0) atomicMax(&s_max, m);
         }
         __syncthreads();
-        // positions [0, s_max) of the range hold every blended splat
-        const int64_t hi = hi_cap < (int64_t)s_max ? hi_cap : (int64_t)s_max;
+        // positions [0, s_max) of the range hold every blended splat; a contributor
+        // count past the range (not one that a blend of it wrote) is cut off
+        const int64_t most = s_max < n ? s_max : n;
+        const int64_t hi = hi_cap < most ? hi_cap : most;
         for (int64_t end = hi; end > lo; end -= kBatch) {
             const int64_t begin = end - kBatch > lo ? end - kBatch : lo;
             const int cnt = (int)(end - begin);
