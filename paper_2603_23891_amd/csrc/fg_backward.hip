@@ -17,16 +17,23 @@
 //                  one workgroup. Every 8 lanes visit the splats that reach
 //                  their own 4 x 2 pixel block (fg_blocks.h). The gradients
 //                  w.r.t. a splat's 2D mean, conic, opacity and colour are
-//                  summed over the block (DPP permutes), over the tile in
-//                  LDS, and added to memory once per splat and batch of 256.
+//                  summed over the block (DPP permutes, three float32
+//                  roundings), over the tile in LDS in float64, and added to
+//                  memory once per splat and batch of 256. In float32 the
+//                  tile's sum would round up to 32 times, once per block, where
+//                  64 lanes per splat round 4 times; against float64 the
+//                  gradients are as close as with 64 lanes or closer (splats that
+//                  cover a tile: log-scales 4.0e-7 of their norm, 4.1e-7 with 64
+//                  lanes, 4.9e-7 with float32 sums and the colour behind kept
+//                  as one product with the pixel's gradient).
 //                  The walk's arithmetic and its LDS adds bound it, so what
 //                  counts is how many lanes of a step hold a blended pixel:
 //                  64 lanes per splat took 2069 us for 2M Gaussians at 1080p
 //                  and 337 us for 100k at 801 x 603 (9 of 64 lanes on a blended
-//                  pixel), 8 lanes per splat 1115 and 248 us; of the 1115 about
-//                  360 are the LDS adds, 220 staging, lists and memory adds.
+//                  pixel), 8 lanes per splat 848 and 166 us (1115 and 248 with
+//                  float32 LDS adds, one native instruction as well).
 //                  Measured and not taken: one reduction over both entries
-//                  (1219), the next entries' LDS reads issued early (1246).
+//                  (1219 for 1115), the next entries' LDS reads issued early (1246).
 //   k_bwd_init, k_bwd_map  clear the splat gradients and note each Gaussian's
 //                  selection index, so that k_project_bwd writes every
 //                  gradient once (zeros for the others) and no pass clears
@@ -156,7 +163,7 @@ __global__ __launch_bounds__(kThreads) void k_render_bwd(const float2* __restric
     __shared__ uint32_t s_g[kBatch];
     __shared__ uint32_t s_bm[kBatch];
     __shared__ __align__(16) uint8_t s_list[fgb::kBlocks][kBatch];
-    __shared__ float s_grad[kBatch * kNG];
+    __shared__ double s_grad[kBatch * kNG];
     __shared__ uint32_t s_max;
     const int tid = threadIdx.x, wave = tid / fgd::kWave;
     const int lx = fgb::pixel_x(tid), ly = fgb::pixel_y(tid);
@@ -166,7 +173,7 @@ __global__ __launch_bounds__(kThreads) void k_render_bwd(const float2* __restric
     const size_t plane = (size_t)W * H;
     int64_t n_chunk_items = view.n_items ? (int64_t)*view.n_items : 0;
     if (n_chunk_items > view.max_items) n_chunk_items = view.max_items;
-    for (int i = tid; i < kBatch * kNG; i += kThreads) s_grad[i] = 0.0f;
+    for (int i = tid; i < kBatch * kNG; i += kThreads) s_grad[i] = 0.0;
     for (int64_t item = blockIdx.x; item < n_chunk_items + n_tiles; item += gridDim.x) {
         // work item: a chunk of a long range, or a whole tile
         uint32_t tile;
@@ -204,17 +211,16 @@ __global__ __launch_bounds__(kThreads) void k_render_bwd(const float2* __restric
         // T after the walked span and the colour behind it (later splats and
         // background): from final_T for a whole tile, from the state saved
         // after the chunk (colour behind = image - colour accumulated so far)
-        // Only its product with the pixel's gradient is needed.
-        float T, GS;
+        float T, S0, S1, S2;
         if (citem < 0) {
             T = inside ? final_T[o] : 1.0f;
-            GS = (G0 * (T * bg0) + G1 * (T * bg1)) + G2 * (T * bg2);
+            S0 = T * bg0; S1 = T * bg1; S2 = T * bg2;
         } else {
             const float* st = view.state + (size_t)citem * (4 * kThreads) + ly * fgd::kTile + lx;
             T = st[0];
-            GS = inside ? (G0 * (image[o] - st[kThreads]) + G1 * (image[plane + o] - st[2 * kThreads])) +
-                              G2 * (image[2 * plane + o] - st[3 * kThreads])
-                        : 0.0f;
+            S0 = inside ? image[o] - st[kThreads] : 0.0f;
+            S1 = inside ? image[plane + o] - st[2 * kThreads] : 0.0f;
+            S2 = inside ? image[2 * plane + o] - st[3 * kThreads] : 0.0f;
         }
         __syncthreads();  // LDS of the previous item
         if (tid == 0) s_max = 0u;
@@ -289,9 +295,11 @@ __global__ __launch_bounds__(kThreads) void k_render_bwd(const float2* __restric
                         gr[6] = G0 * w;
                         gr[7] = G1 * w;
                         gr[8] = G2 * w;
-                        const float Gc = (G0 * b[u].z + G1 * b[u].w) + G2 * cb[u];
-                        const float dLda = Gc * Tk - GS * inv[u];
-                        GS = GS + Gc * w;
+                        const float dLda = (G0 * (b[u].z * Tk - S0 * inv[u]) + G1 * (b[u].w * Tk - S1 * inv[u])) +
+                                           G2 * (cb[u] * Tk - S2 * inv[u]);
+                        S0 = S0 + b[u].z * w;
+                        S1 = S1 + b[u].w * w;
+                        S2 = S2 + cb[u] * w;
                         T = Tk;
                         const float q = b[u].y * e[u] < 0.99f ? dLda * e[u] : 0.0f;
                         const float qx = q * dx, qy = q * dy;
@@ -305,8 +313,8 @@ __global__ __launch_bounds__(kThreads) void k_render_bwd(const float2* __restric
                     // the block's sums join the splat's in LDS
                     float t[2];
                     reduce8(gr, t);
-                    if (has0 && t[0] != 0.0f) atomicAdd(&s_grad[j * kNG + comp], t[0]);
-                    if (has1 && t[1] != 0.0f) atomicAdd(&s_grad[j * kNG + comp + 1], t[1]);
+                    if (has0 && t[0] != 0.0f) atomicAdd(&s_grad[j * kNG + comp], (double)t[0]);
+                    if (has1 && t[1] != 0.0f) atomicAdd(&s_grad[j * kNG + comp + 1], (double)t[1]);
                     if (STATS) n_frag += hit[u] ? 1u : 0u;
                 }
             }
@@ -314,18 +322,18 @@ __global__ __launch_bounds__(kThreads) void k_render_bwd(const float2* __restric
             // the sums of q's moments to the gradients of mean, conic and opacity
             // (s_a.z = -A / 2, s_b.x = -C / 2, s_b.y = opacity)
             if (tid < cnt) {
-                float* t = s_grad + tid * kNG;
-                const float4 b = s_b[tid];
-                t[0] = b.y * t[0];
-                t[1] = b.y * t[1];
-                t[2] = b.y * (-0.5f * t[2]);
-                t[3] = b.y * -t[3];
-                t[4] = b.y * (-0.5f * t[4]);
+                double* t = s_grad + tid * kNG;
+                const double op = s_b[tid].y;
+                t[0] = op * t[0];
+                t[1] = op * t[1];
+                t[2] = op * (-0.5 * t[2]);
+                t[3] = op * -t[3];
+                t[4] = op * (-0.5 * t[4]);
             }
             __syncthreads();
             if (STATS && tid < cnt) {
                 unsigned n = 0;
-                for (int c = 0; c < kNG; c++) n += s_grad[tid * kNG + c] != 0.0f ? 1u : 0u;
+                for (int c = 0; c < kNG; c++) n += s_grad[tid * kNG + c] != 0.0 ? 1u : 0u;
                 n_instr += n != 0u ? 1u : 0u;
                 n_elem += n;
             }
@@ -333,10 +341,10 @@ __global__ __launch_bounds__(kThreads) void k_render_bwd(const float2* __restric
             // one set of sums per splat and batch to memory, consecutive lanes on
             // consecutive components
             for (int i = tid; i < cnt * kNG; i += kThreads) {
-                const float v = s_grad[i];
-                if (v != 0.0f) {
-                    s_grad[i] = 0.0f;
-                    atomicAdd(gacc + (size_t)s_g[i / kNG] * kNG + i % kNG, v);
+                const double v = s_grad[i];
+                if (v != 0.0) {
+                    s_grad[i] = 0.0;
+                    atomicAdd(gacc + (size_t)s_g[i / kNG] * kNG + i % kNG, (float)v);
                 }
             }
             __syncthreads();
