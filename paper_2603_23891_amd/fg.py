@@ -172,15 +172,21 @@ def camera_array(cams):
     return (FgCamera * len(cams))(*[camera_struct(c) for c in cams]), len(cams)
 
 
+def _floats(v):
+    """The float32 values of a camera field, one per row (a column converts row by row)."""
+    a = np.asarray(v, np.float32)
+    return a.tolist() if a.ndim == 1 else [float(x) for x in a]
+
+
 def camera_struct(cam) -> FgCamera:
     if isinstance(cam, _Cameras):
         if cam.n != 1:
             raise TypeError("one camera expected")
         return cam.array[0]
     c = FgCamera()
-    c.R[:] = np.asarray(cam.R, np.float32).tolist()
-    c.t[:] = np.asarray(cam.t, np.float32).tolist()
-    c.campos[:] = np.asarray(cam.campos, np.float32).tolist()
+    c.R[:] = _floats(cam.R)
+    c.t[:] = _floats(cam.t)
+    c.campos[:] = _floats(cam.campos)
     c.fx, c.fy, c.cx, c.cy = cam.fx, cam.fy, cam.cx, cam.cy
     c.width, c.height = cam.width, cam.height
     c.znear, c.kx, c.ky = cam.znear, cam.kx, cam.ky
