@@ -411,7 +411,6 @@ class FrameBuffers:
         self.sel_bits = torch.empty(max((N + 31) // 32, 1), dtype=i32, device=device)
         self.sel_idx = torch.empty(max(self.cap_sel, 1), dtype=i32, device=device)
         self.counts = torch.zeros(4, dtype=i32, device=device)  # n_sel, n_pairs, status, spare
-        self._n_sel, self._n_pairs, self._status = self.counts[0:1], self.counts[1:2], self.counts[2:3]
         self.filter_ws = torch.empty(fg_filter_workspace_size(N, tree.n_internal_span), dtype=torch.uint8,
                                      device=device)
         self.splats = Splats(self.cap_sel, device)
@@ -432,6 +431,15 @@ class FrameBuffers:
         self.image = torch.empty((3, height, width), dtype=torch.float32, device=device)
         self.final_T = torch.empty((height, width), dtype=torch.float32, device=device)
         self.n_contrib = torch.empty((height, width), dtype=i32, device=device)
+
+    @property
+    def counts(self):
+        return self._counts
+
+    @counts.setter
+    def counts(self, t):
+        # the views are made once, not on each of a frame's calls
+        self._counts, self._n_sel, self._n_pairs, self._status = t, t[0:1], t[1:2], t[2:3]
 
     @property
     def n_sel(self):

@@ -1,5 +1,7 @@
 """The Python binding's host side, without a GPU: camera values in every form that
 converts to float32, one by one."""
+from types import SimpleNamespace
+
 import numpy as np
 import pytest
 import torch
@@ -35,3 +37,15 @@ def test_camera_of_the_wrong_size_is_refused():
         with pytest.raises((TypeError, ValueError)):
             fg.camera_struct(bad)
     assert fg.camera_struct(cam).width == 64
+
+
+def test_counts_may_be_replaced():
+    """n_sel, n_pairs and status are those of the counts tensor in place."""
+    tree = SimpleNamespace(n_nodes=100, n_internal_span=10)
+    fb = fg.FrameBuffers(tree, 64, 48, 50, 200, device="cpu")
+    for counts in (fb.counts, torch.tensor([7, 8, 9, 0], dtype=torch.int32), torch.zeros(8, dtype=torch.int32)[2:6]):
+        fb.counts = counts
+        for k, t in enumerate((fb.n_sel, fb.n_pairs, fb.status)):
+            assert t.data_ptr() == counts.data_ptr() + 4 * k and t.shape == (1,)
+    fb.counts[:3] = torch.tensor([3, 4, 2], dtype=torch.int32)
+    assert fg.read_counts(fb) == (3, 4, 2) and int(fb.n_pairs) == 4
