@@ -324,11 +324,14 @@ __global__ __launch_bounds__(kThreads) void k_render_bwd(const float2* __restric
             if (tid < cnt) {
                 double* t = s_grad + tid * kNG;
                 const double op = s_b[tid].y;
-                t[0] = op * t[0];
-                t[1] = op * t[1];
-                t[2] = op * (-0.5 * t[2]);
-                t[3] = op * -t[3];
-                t[4] = op * (-0.5 * t[4]);
+                // a sum of nothing stays zero where the opacity is not finite (such a
+                // splat's alpha is the cap, which passes no gradient)
+                auto times = [op](double v) { return v != 0.0 ? op * v : 0.0; };
+                t[0] = times(t[0]);
+                t[1] = times(t[1]);
+                t[2] = times(-0.5 * t[2]);
+                t[3] = times(-t[3]);
+                t[4] = times(-0.5 * t[4]);
             }
             __syncthreads();
             if (STATS && tid < cnt) {
