@@ -945,8 +945,8 @@ __global__ __launch_bounds__(kThreads) void k_render_long(const float2* __restri
 }
 
 // The first mask_blocks workgroups make the long tiles' pass masks; the others
-// blend the tiles that hold splats and are not long, one each, heavy ones
-// first (those past the last find nothing). One launch, since the two need
+// blend the tiles that hold splats and are not long, from the first-th on, one
+// each, heavy ones first (those past the last find nothing). One launch, since the two need
 // nothing of each other and neither fills the chip by itself in most frames.
 // The dispatcher balances the tiles: a work ticket (one atomic per tile, all
 // on one address) took longer than the tiles themselves in frames of few
@@ -957,7 +957,7 @@ __global__ __launch_bounds__(kThreads) void k_render(const float2* __restrict__ 
                                                      const uint32_t* __restrict__ vals,
                                                      const uint32_t* __restrict__ ranges, int64_t n_tiles,
                                                      RenderViews V, float bg0, float bg1, float bg2, RenderWs ws,
-                                                     uint32_t mask_blocks, float* __restrict__ image,
+                                                     uint32_t mask_blocks, uint32_t first, float* __restrict__ image,
                                                      float* __restrict__ final_T, uint32_t* __restrict__ n_contrib,
                                                      unsigned long long* __restrict__ frag_stats)
 {
@@ -969,7 +969,7 @@ __global__ __launch_bounds__(kThreads) void k_render(const float2* __restrict__ 
         make_masks<CHUNK, STATS>(s.mask, blockIdx.x, mask_blocks, xy, conic_o, vals, ranges, V, ws, frag_stats);
         return;
     }
-    const uint32_t item = blockIdx.x - mask_blocks, n_heavy = ws.counters[kCntHeavy];
+    const uint32_t item = first + (blockIdx.x - mask_blocks), n_heavy = ws.counters[kCntHeavy];
     if (item >= ws.counters[kCntTiles]) return;
     const bool heavy = item < n_heavy;
     const uint32_t tile = ws.order[heavy ? (int64_t)item : n_tiles - 1 - (int64_t)(item - n_heavy)];
@@ -1052,19 +1052,30 @@ void launch(const fg_splats* splats, const uint32_t* vals, const uint32_t* range
     const float4* rgb = (const float4*)splats->rgb_depth;
     const unsigned gm = (unsigned)(max_mask_items < 2048 ? (max_mask_items < 1 ? 1 : max_mask_items) : 2048);
     const unsigned gl = (unsigned)(2 * n_tiles < 4096 ? 2 * n_tiles : 4096);
-    const unsigned gr = gm + (unsigned)n_tiles;
+    // a grid holds fewer than 2^32 threads: one launch up to 16.7 million tiles
+    auto blend = [&](auto kernel) {
+        const int64_t most = (((int64_t)1 << 32) - 1) / kThreads;
+        unsigned masks = gm;
+        for (int64_t t = 0; t < n_tiles;) {
+            const int64_t n = n_tiles - t < most - masks ? n_tiles - t : most - masks;
+            hipLaunchKernelGGL(kernel, dim3(masks + (unsigned)n), dim3(kThreads), 0, s, xy, co, rgb, vals, ranges, n_tiles,
+                               V, bg[0], bg[1], bg[2], w, masks, (uint32_t)t, image, final_T, n_contrib, frag_stats);
+            t += n;
+            masks = 0;
+        }
+    };
+    auto blend_long = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(gl), dim3(kThreads), 0, s, xy, co, rgb, vals, ranges, V, bg[0], bg[1], bg[2], w,
+                           image, final_T, n_contrib, frag_stats);
+    };
     if (frag_stats) {
-        hipLaunchKernelGGL((k_render<CHUNK, true>), dim3(gr), dim3(kThreads), 0, s, xy, co, rgb, vals, ranges, n_tiles,
-                           V, bg[0], bg[1], bg[2], w, gm, image, final_T, n_contrib, frag_stats);
-        hipLaunchKernelGGL((k_render_long<CHUNK, true>), dim3(gl), dim3(kThreads), 0, s, xy, co, rgb, vals, ranges, V,
-                           bg[0], bg[1], bg[2], w, image, final_T, n_contrib, frag_stats);
+        blend(k_render<CHUNK, true>);
+        blend_long(k_render_long<CHUNK, true>);
     } else {
         const bool timed = tune && tune->blend_events[0] && tune->blend_events[1];
         if (timed) (void)hipEventRecord((hipEvent_t)tune->blend_events[0], s);
-        hipLaunchKernelGGL((k_render<CHUNK, false>), dim3(gr), dim3(kThreads), 0, s, xy, co, rgb, vals, ranges, n_tiles,
-                           V, bg[0], bg[1], bg[2], w, gm, image, final_T, n_contrib, frag_stats);
-        hipLaunchKernelGGL((k_render_long<CHUNK, false>), dim3(gl), dim3(kThreads), 0, s, xy, co, rgb, vals, ranges, V,
-                           bg[0], bg[1], bg[2], w, image, final_T, n_contrib, frag_stats);
+        blend(k_render<CHUNK, false>);
+        blend_long(k_render_long<CHUNK, false>);
         if (timed) (void)hipEventRecord((hipEvent_t)tune->blend_events[1], s);
     }
 }
