@@ -45,29 +45,50 @@ struct RenderWs {
     uint32_t* counters;   // see the kCnt* indices
     uint32_t* masks;      // [max_items][CHUNK/32][256] pass masks of the long tiles' chunks
     float* state;         // with save_state: [max_items][4][256] T, C0, C1, C2 after each chunk; else null
-    uint32_t* sched;      // [3][tile blocks] block totals of the many-tile schedule
+    uint32_t* sched;      // [tile blocks][4] block totals of the many-tile schedule
 };
 
 // counters[]: heavy tiles, chunk items (clamped to max_items), tiles with
 // splats, chunks from which a tile is long.
-//
-// Walking a tile's batches one after another costs about 15 us per batch on
-// the tile's own (the crowded pixel rows of a horizon keep few lanes busy), but
-// 40 % of the work of masks and a second walk. So tiles are long from two
-// chunks on where heavy tiles average four chunks or more (a horizon), or where
-// all chunks together are too few to fill the chip; otherwise (many tiles of
-// much the same length) only tiles of 12 chunks. k_render + k_render_long, both
-// ways: 1M-leaf city (842 chunks on 184 tiles) 97 us long from 2, 290 us from
-// 12; 2M Gaussians in training (21487 on 6937) 1000 us and 343 us.
 enum { kCntHeavy, kCntItems, kCntTiles, kCntLongChunks };
 
+// From how many chunks on a tile is long. Walking a tile's batches one after
+// another costs 10 to 20 us per 256 splats on the tile's own (the crowded pixel
+// rows of a horizon keep few lanes busy), but about half the work of masks
+// and a second walk. So what counts is whether the heavy tiles fill the chip
+// by themselves (k_render + k_render_long, us, long from 2 chunks on and by the
+// batches):
+//  - many of much the same length (items^2 over the sum of squares, the number
+//    of equal tiles that they amount to, is 900 or more and at least three
+//    quarters of the heavy tiles): only tiles of 12 x 256 splats, or of a
+//    thousandth of all chunks, whose own walk takes about as long as all of
+//    them together. Training views: 1000 and 343 for 2M Gaussians at 1080p, 625
+//    and 333 at 720p, 359 and 255 for 1M at 960 x 540; lists of 3 to 6 chunks
+//    on 8000 tiles 2757 and 1187 (128-splat chunks 3822 and 1306). At 640 x 360
+//    (766 equal tiles) it is 204 and 252;
+//  - of four chunks or more on average (a horizon), or all chunks together too
+//    few to fill the chip: from two chunks on. 1M-leaf city (842 chunks on 184
+//    tiles) 97 and 290; 20M nodes at 1440p (1017 equal tiles of 1982) 381 and 416;
+//  - otherwise only tiles of 12 chunks.
+constexpr float kAlikeTiles = 900.0f, kAlikeShare = 0.75f;
+
+__device__ __forceinline__ uint32_t long_chunks(uint32_t heavy, uint32_t items, float squares, int chunk)
+{
+    const float equal = (float)heavy >= kAlikeTiles ? (float)items * (float)items / squares : 0.0f;
+    if (equal >= kAlikeTiles && equal >= kAlikeShare * (float)heavy) {
+        const uint32_t least = 12u * 256u / (uint32_t)chunk, share = items / 1000u;
+        return share > least ? share : least;
+    }
+    return items >= 4u * heavy || items < 1024u ? 2u : 12u;
+}
+
 __device__ __forceinline__ void init_counters(uint32_t* __restrict__ counters, uint32_t heavy, uint32_t items,
-                                              uint32_t tiles, int64_t max_items)
+                                              uint32_t tiles, float squares, int chunk, int64_t max_items)
 {
     counters[kCntHeavy] = heavy;
     counters[kCntItems] = (int64_t)items < max_items ? items : (uint32_t)max_items;
     counters[kCntTiles] = tiles;
-    counters[kCntLongChunks] = items >= 4u * heavy || items < 1024u ? 2u : 12u;
+    counters[kCntLongChunks] = long_chunks(heavy, items, squares, chunk);
 }
 
 struct Frag {
@@ -200,6 +221,7 @@ __global__ __launch_bounds__(kScanThreads) void k_schedule(const uint32_t* __res
     __shared__ uint32_t s_carry_m;
     __shared__ uint32_t s_c[8 * kScanThreads];
     const int tid = threadIdx.x, lane = fgd::lane_id(), wave = tid / fgd::kWave;
+    float squares = 0.0f;  // of the heavy tiles' chunk counts
     if (tid == 0) {
         s_carry = 0ull;
         s_carry_m = 0u;
@@ -227,6 +249,7 @@ __global__ __launch_bounds__(kScanThreads) void k_schedule(const uint32_t* __res
             if (c[k] > 1) {
                 sum += 1ull;
                 msum += c[k];
+                squares += (float)c[k] * (float)c[k];
             } else if (c[k] == 1) {
                 sum += 1ull << 32;
             }
@@ -281,18 +304,26 @@ __global__ __launch_bounds__(kScanThreads) void k_schedule(const uint32_t* __res
         }
         __syncthreads();
     }
-    if (tid == 0) {
-        const uint32_t heavy = (uint32_t)s_carry;
-        init_counters(counters, heavy, s_carry_m, heavy + (uint32_t)(s_carry >> 32), max_mask_items);
+    const uint32_t heavy = (uint32_t)s_carry;
+    if ((float)heavy >= kAlikeTiles) {  // else the squares decide nothing
+#pragma unroll
+        for (int d = fgd::kWave / 2; d > 0; d >>= 1) squares += __shfl_xor(squares, d, fgd::kWave);
+        if (lane == 0) s_wave_m[wave] = __float_as_uint(squares);
+        __syncthreads();
+        squares = 0.0f;
+        for (int w = 0; w < kScanThreads / fgd::kWave; w++) squares += __uint_as_float(s_wave_m[w]);
     }
+    if (tid == 0)
+        init_counters(counters, heavy, s_carry_m, heavy + (uint32_t)(s_carry >> 32), squares, CHUNK, max_mask_items);
 }
 
 // The same schedule for many tiles (a batch of views), in three launches:
 // per block of 8192 tiles the chunk counts and the block's totals (heavy
-// tiles, light tiles, mask items); one workgroup scans the block totals; each
-// block then writes its part of order[] and mfirst[] from its base. Results
-// equal k_schedule's.
+// tiles, light tiles, mask items, squares of chunk counts); one workgroup scans
+// the block totals; each block then writes its part of order[] and mfirst[] from
+// its base. Results equal k_schedule's.
 constexpr int kSchedTiles = 8 * kScanThreads;
+constexpr int kSchedWords = 4;
 
 template <int CHUNK>
 __global__ __launch_bounds__(kScanThreads) void k_sched_count(const uint32_t* __restrict__ ranges, int64_t n_tiles,
@@ -301,9 +332,11 @@ __global__ __launch_bounds__(kScanThreads) void k_sched_count(const uint32_t* __
 {
     __shared__ uint32_t s_h[kScanThreads / fgd::kWave], s_l[kScanThreads / fgd::kWave],
         s_m[kScanThreads / fgd::kWave];
+    __shared__ float s_q[kScanThreads / fgd::kWave];
     const int tid = threadIdx.x, lane = fgd::lane_id(), wave = tid / fgd::kWave;
     const int64_t base = (int64_t)blockIdx.x * kSchedTiles;
     uint32_t h = 0, l = 0, m = 0;
+    float q = 0.0f;
 #pragma unroll
     for (int k = 0; k < 8; k++) {
         const int64_t t = base + (int64_t)tid * 8 + k;
@@ -312,6 +345,7 @@ __global__ __launch_bounds__(kScanThreads) void k_sched_count(const uint32_t* __
         if (c > 1) {
             h += 1u;
             m += c;
+            q += (float)c * (float)c;
         } else if (c == 1) {
             l += 1u;
         }
@@ -321,42 +355,51 @@ __global__ __launch_bounds__(kScanThreads) void k_sched_count(const uint32_t* __
         h += __shfl_xor(h, d, fgd::kWave);
         l += __shfl_xor(l, d, fgd::kWave);
         m += __shfl_xor(m, d, fgd::kWave);
+        q += __shfl_xor(q, d, fgd::kWave);
     }
     if (lane == 0) {
         s_h[wave] = h;
         s_l[wave] = l;
         s_m[wave] = m;
+        s_q[wave] = q;
     }
     __syncthreads();
     if (tid == 0) {
         uint32_t th = 0, tl = 0, tm = 0;
+        float tq = 0.0f;
         for (int w = 0; w < kScanThreads / fgd::kWave; w++) {
             th += s_h[w];
             tl += s_l[w];
             tm += s_m[w];
+            tq += s_q[w];
         }
-        bsum[3 * blockIdx.x] = th;
-        bsum[3 * blockIdx.x + 1] = tl;
-        bsum[3 * blockIdx.x + 2] = tm;
+        uint32_t* b = bsum + kSchedWords * blockIdx.x;
+        b[0] = th;
+        b[1] = tl;
+        b[2] = tm;
+        b[3] = __float_as_uint(tq);
     }
 }
 
 // One thread: exclusive scan of the blocks' totals in place, and the counters.
-__global__ void k_sched_scan(uint32_t* __restrict__ bsum, int64_t nb, int64_t max_mask_items,
+__global__ void k_sched_scan(uint32_t* __restrict__ bsum, int64_t nb, int chunk, int64_t max_mask_items,
                              uint32_t* __restrict__ counters)
 {
     if (threadIdx.x != 0) return;
     uint32_t h = 0, l = 0, m = 0;
-    for (int64_t b = 0; b < nb; b++) {
-        const uint32_t a0 = bsum[3 * b], a1 = bsum[3 * b + 1], a2 = bsum[3 * b + 2];
-        bsum[3 * b] = h;
-        bsum[3 * b + 1] = l;
-        bsum[3 * b + 2] = m;
+    float q = 0.0f;
+    for (int64_t i = 0; i < nb; i++) {
+        uint32_t* b = bsum + kSchedWords * i;
+        const uint32_t a0 = b[0], a1 = b[1], a2 = b[2];
+        q += __uint_as_float(b[3]);
+        b[0] = h;
+        b[1] = l;
+        b[2] = m;
         h += a0;
         l += a1;
         m += a2;
     }
-    init_counters(counters, h, m, h + l, max_mask_items);
+    init_counters(counters, h, m, h + l, q, chunk, max_mask_items);
 }
 
 template <int CHUNK>
@@ -399,9 +442,9 @@ __global__ __launch_bounds__(kScanThreads) void k_sched_write(int64_t n_tiles, c
         s_wave_m[wave] = xm;
     }
     __syncthreads();
-    unsigned long long run = (unsigned long long)bsum[3 * blockIdx.x] |
-                             ((unsigned long long)bsum[3 * blockIdx.x + 1] << 32);
-    uint32_t mf = bsum[3 * blockIdx.x + 2];
+    const uint32_t* b = bsum + kSchedWords * blockIdx.x;
+    unsigned long long run = (unsigned long long)b[0] | ((unsigned long long)b[1] << 32);
+    uint32_t mf = b[2];
     for (int w = 0; w < wave; w++) {
         run += s_wave[w];
         mf += s_wave_m[w];
@@ -1008,7 +1051,7 @@ size_t carve(void* base, int64_t n_tiles, int64_t cap_pairs, int chunk, bool sav
     if (mask_items > 0 && mask_items < cap) cap = mask_items;
     *max_items = need < cap ? need : cap;
     const size_t state_bytes = save_state ? (size_t)*max_items * 4 * kThreads * 4 : 0;
-    const size_t sched_bytes = (size_t)3 * 4 * (size_t)((n_tiles + kSchedTiles - 1) / kSchedTiles + 1);
+    const size_t sched_bytes = (size_t)kSchedWords * 4 * (size_t)((n_tiles + kSchedTiles - 1) / kSchedTiles + 1);
     const size_t sizes[8] = {(size_t)n_tiles * 4, (size_t)n_tiles * 4, (size_t)n_tiles * 4, (size_t)*max_items * 4, 64,
                              (size_t)*max_items * (size_t)mask_bytes, state_bytes, sched_bytes};
     void** dst[8] = {(void**)&w->nch, (void**)&w->mfirst, (void**)&w->order, (void**)&w->mitem, (void**)&w->counters,
@@ -1038,7 +1081,7 @@ void launch(const fg_splats* splats, const uint32_t* vals, const uint32_t* range
         const int64_t nb = (n_tiles + kSchedTiles - 1) / kSchedTiles;
         hipLaunchKernelGGL(k_sched_count<CHUNK>, dim3((unsigned)nb), dim3(kScanThreads), 0, s, ranges, n_tiles, w.nch,
                            w.sched);
-        hipLaunchKernelGGL(k_sched_scan, dim3(1), dim3(64), 0, s, w.sched, nb, max_mask_items, w.counters);
+        hipLaunchKernelGGL(k_sched_scan, dim3(1), dim3(64), 0, s, w.sched, nb, CHUNK, max_mask_items, w.counters);
         hipLaunchKernelGGL(k_sched_write<CHUNK>, dim3((unsigned)nb), dim3(kScanThreads), 0, s, n_tiles, w.nch,
                            w.sched, w.mfirst, w.order);
     }
