@@ -734,7 +734,8 @@ size_t carve(void* base, int64_t sel_items, int64_t cap_items, int64_t cap_pairs
     }
     if (base) {
         w->rect_d = reinterpret_cast<ushort4*>(w->d1);
-        w->slices.n = reinterpret_cast<unsigned long long*>(w->counts + 2);
+        // 8-byte aligned for its atomics, whatever the workspace's own alignment
+        w->slices.n = reinterpret_cast<unsigned long long*>(((uintptr_t)(w->counts + 2) + 7) & ~(uintptr_t)7);
     }
     return off;
 }
