@@ -402,16 +402,19 @@ __device__ __forceinline__ void sh_basis_and_grad(float x, float y, float z, flo
 }
 
 template <int D>
-__global__ __launch_bounds__(256) void k_project_bwd(fg_params prm, fgd::Cam cam, const float* __restrict__ gacc,
-                                                     fg_grads out)
+__global__ __launch_bounds__(256) void k_project_bwd(fg_params prm, fgd::Cam cam, const uint32_t* __restrict__ n_sel_p,
+                                                     int64_t cap_sel, const float* __restrict__ gacc, fg_grads out)
 {
     constexpr int K = (D + 1) * (D + 1);
     const int64_t m = prm.m;
+    int64_t n_sel = (int64_t)*n_sel_p;
+    if (n_sel > cap_sel) n_sel = cap_sel;
     for (int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; g < m; g += (int64_t)gridDim.x * blockDim.x) {
         // the map lies in the logit gradients: this thread's own entry is read
-        // here and written below
+        // here and written below (an entry that is no index, as where a caller's
+        // outputs overlap, reads nothing)
         const int32_t i = __float_as_int(out.logit[g]);
-        if (i < 0) {
+        if (i < 0 || i >= n_sel) {
             for (int a = 0; a < 3; a++) out.mean[a * m + g] = 0.0f;
             for (int a = 0; a < 3; a++) out.log_scale[a * m + g] = 0.0f;
             for (int a = 0; a < 4; a++) out.quat[a * m + g] = 0.0f;
@@ -650,10 +653,10 @@ extern "C" int fg_render_backward(const fg_params* p, const fg_camera* cam, cons
     const fgd::Cam c = fgd::make_cam(*cam);
     const dim3 g = blocks_for(m, 8192), b(256);
     switch (p->sh_degree) {
-        case 0: hipLaunchKernelGGL(k_project_bwd<0>, g, b, 0, s, *p, c, gacc, *out); break;
-        case 1: hipLaunchKernelGGL(k_project_bwd<1>, g, b, 0, s, *p, c, gacc, *out); break;
-        case 2: hipLaunchKernelGGL(k_project_bwd<2>, g, b, 0, s, *p, c, gacc, *out); break;
-        default: hipLaunchKernelGGL(k_project_bwd<3>, g, b, 0, s, *p, c, gacc, *out); break;
+        case 0: hipLaunchKernelGGL(k_project_bwd<0>, g, b, 0, s, *p, c, n_sel, cap_sel, gacc, *out); break;
+        case 1: hipLaunchKernelGGL(k_project_bwd<1>, g, b, 0, s, *p, c, n_sel, cap_sel, gacc, *out); break;
+        case 2: hipLaunchKernelGGL(k_project_bwd<2>, g, b, 0, s, *p, c, n_sel, cap_sel, gacc, *out); break;
+        default: hipLaunchKernelGGL(k_project_bwd<3>, g, b, 0, s, *p, c, n_sel, cap_sel, gacc, *out); break;
     }
     return hipGetLastError() == hipSuccess ? FG_OK : FG_ERR_HIP;
 }
