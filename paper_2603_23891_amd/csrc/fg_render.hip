@@ -754,8 +754,10 @@ __device__ __forceinline__ void blend_batches(Staged& st, const RenderWs& ws, co
 
 // ---- the walk of a long tile ---------------------------------------------------
 
-// alpha of a fragment that passed the skip tests (so -5.6 <= power <= 0):
-// the same expressions as pixel_alpha, hence the same value.
+// alpha of a fragment that passed the skip tests (so -5.6 <= power <= 0). Its
+// power is fgb::eval_alpha's, which scales the conic's diagonal by -0.5 before
+// the products where this scales their sum: a power of two, exact unless a product
+// is denormal, and then the exponential is 1 either way.
 __device__ __forceinline__ float passed_alpha(float2 mm, float4 co, float fpx, float fpy)
 {
     const float dx = mm.x - fpx;
@@ -837,8 +839,7 @@ __device__ __forceinline__ void walk_masks(const uint32_t* mcol, const float2* s
 }
 
 // Register copy of one chunk for one wave of a long tile: the splat records
-// this lane stages (every 64th of the chunk) and the mask words of its pixel
-// (zero where the masks are computed in place).
+// this lane stages (every 64th of the chunk) and the mask words of its pixel.
 template <int CHUNK>
 struct ChunkRegs {
     static constexpr int S = CHUNK / fgd::kWave;
