@@ -455,9 +455,9 @@ def measure_fwd_bwd(torch):
     torch.cuda.synchronize()
     blended = int(stats[3].item())
     bwd_ms = e[1].elapsed_time(e[2])
-    # the blend backward's own counters on the same frame: its gradient atomic
-    # instructions (one per wave and splat with a blended pixel), the elements
-    # they add, and the fragments it walks
+    # the blend backward's own counters on the same frame: the splat gradients it
+    # adds to memory (one per splat and batch of a range with a blended pixel),
+    # the elements those hold, and the fragments it walks
     bstats = torch.zeros(3, dtype=torch.int64, device="cuda")
     r.tune.bwd_stats = bstats.data_ptr()
     r.backward(*dev, views[3], dl)
@@ -665,7 +665,7 @@ def main():
     K = args.steps
     evs = [[torch.cuda.Event(enable_timing=True) for _ in range(5)] for _ in range(K)]
     torch.cuda.synchronize()
-    # events the library records on its stream right around its blend kernel
+    # events the library records on its stream right around its blend kernels
     bev = [(torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)) for _ in range(K)]
     for a, b in bev:  # create the underlying events
         a.record(stream)

@@ -31,7 +31,7 @@
  *    view, counts n_sel[v]; fg_sort and fg_render treat the views as one
  *    frame whose tiles have consecutive global ids (cams[v].tile_base =
  *    cams[v-1].tile_base + tiles of view v-1), so one pair list, one range
- *    array and one blend launch serve them all. fg_filter and fg_preprocess
+ *    array and one blend serve them all. fg_filter and fg_preprocess
  *    also accept cams_dev, a device copy of the cameras whose pose (R, t,
  *    campos) the kernels read at run time, so that a captured graph replays
  *    with poses written into it between replays (intrinsics and sizes are
@@ -375,8 +375,8 @@ int fg_render(const fg_splats* splats, const uint32_t* vals, const uint32_t* ran
  *       of its tile of alpha * T for the pixels that blend that splat (the
  *       tests and termination of Eq. (2), as fg_render; fragments skipped or
  *       never reached add nothing). Each pixel's terms are float32 products
- *       identical to the sequential blend's; their sum is float32 in an
- *       unspecified order.
+ *       identical to the sequential blend's; their sum is float32 in one
+ *       order of 9 roundings, the same in every run and in both walks.
  *   tile_gtc [n_tiles] (device): the tile's GTC, Eq. (6), the mean KPC over
  *       all pairs of the tile, zero contributions included; NaN for a tile
  *       without pairs (0/0).
@@ -461,8 +461,9 @@ size_t fg_render_backward_workspace_size(int64_t cap_sel);
  * to front with the transmittance recovered from final_T
  * (T_k = T_{k+1} / (1 - alpha_k)); alpha capped at 0.99 passes no gradient to
  * opacity or position; the tile rectangle and shrink radius are piecewise
- * constant and pass none. Gradients are summed with float32 atomics, so the
- * summation order (and the last bits) vary between runs.
+ * constant and pass none. A splat's gradients are summed over 256 entries of a
+ * tile in float64 and over tiles with float32 atomics, so the summation
+ * order (and the last bits) vary between runs.
  * image, render_ws (render_ws_bytes), cap_pairs, tune: that frame's image and
  * the workspace, pair capacity and tune its fg_render call used. When tune
  * has save_state, the chunks of long ranges are walked in parallel, each

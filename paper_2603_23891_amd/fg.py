@@ -197,9 +197,9 @@ def camera_struct(cam) -> FgCamera:
 def tune_struct(render_batch: int = 0, radix_bits: int = 0, save_state: bool = False, blend_events=None,
                 mask_items: int = 0, bwd_stats: Optional[torch.Tensor] = None) -> FgTune:
     """blend_events: None, or two recorded torch.cuda.Event (timing enabled)
-    that fg_render records around its blend kernel. bwd_stats: None, or an
+    that fg_render records around its blend kernels. bwd_stats: None, or an
     int64 device tensor of at least 3 entries that fg_render_backward adds its
-    counters to (atomic instructions, gradient elements, blended fragments)."""
+    counters to (splat gradients added, their elements, blended fragments)."""
     t = FgTune(render_batch=render_batch, radix_bits=radix_bits, save_state=1 if save_state else 0,
                mask_items=mask_items)
     if blend_events is not None:
